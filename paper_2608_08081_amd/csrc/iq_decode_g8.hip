@@ -292,147 +292,11 @@ struct G8Smem {
   G8Stage<kBits, kSepO> st;
 };
 
-// Writes the fp16 pair table of the codebook (threads 0 .. 2^(2b) - 1).
-template <class Smem, int kBits>
-__device__ __forceinline__ void build_pair_table(Smem& sm, const CodebookB<kBits>& cb, int tid) {
-  constexpr int kLut = 1 << (2 * kBits);
-  if (tid < kLut) {
-    constexpr int kMask = (1 << kBits) - 1;
-    const uint32_t lo =
-        __builtin_bit_cast(uint16_t, static_cast<_Float16>(codebook_level(cb, tid & kMask)));
-    const uint32_t hi =
-        __builtin_bit_cast(uint16_t, static_cast<_Float16>(codebook_level(cb, tid >> kBits)));
-    sm.lut[tid] = lo | (hi << 16);
-  }
-}
-
-// The kernel's arguments, as passed (see decode_g8_kernel).
+// The new token's partial of row bgv: the row's last, after its splits.
 template <int kBits>
-struct G8Args {
-  const float* q;
-  uint8_t* k_codes;
-  float* k_norms;
-  uint8_t* v_codes;
-  float* v_norms;
-  const int32_t* seq_lens;
-  const float* quats;
-  float* partials;
-  float* out;
-  int64_t capacity;
-  int max_seq_len, n_kv_heads, n_splits, split_len;
-  float qscale;
-  CodebookB<kBits> cb;
-  const void* k_new;
-  const void* v_new;
-  int new_f16;
-  int32_t* status;
-  PageTable pages;
-  int group, batch;
-  int32_t* lens0;   // fused steps on grids of several rounds: each sequence's length
-};
-
-// The fused step's new token for (sequence b, KV head g, head group vg):
-// compresses the new key and value (Alg. 1), writes their records at
-// position seq_lens[b] and publishes the new token's score and value as the
-// partial of split index n_splits (m = -inf when the token is not attended:
-// at capacity, or at or past max_seq_len).  No attention work reads the
-// records being written, and seq_lens is advanced by the merge kernel after
-// every workgroup has read it.  lens0 (grids of several rounds): the
-// sequence's length as read here, for the merge.
-template <bool kPaged, int kBits, bool kRope, class Smem>
-__device__ __forceinline__ void append_token(Smem& sm, const G8Args<kBits>& a,
-                                             int gsize, int g, int vg, int b, int bgv,
-                                             bool build_lut) {
-  constexpr int kRB = record_bytes<kBits>();
-  int tid = threadIdx.x;
-  asm volatile("" : "+v"(tid));   // recomputed per item (see attend_split)
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int lane = tid & 63;
-  const int n_q_heads = a.n_kv_heads * gsize;
-  const int hq0 = g * gsize + kHeads * vg;
-  const int nh = gsize - kHeads * vg < kHeads ? gsize - kHeads * vg : kHeads;
-  const int n_parts = a.n_splits + 1;
-  const int qh = (tid >> 5) & 7, qblk = tid & 31;
-  const f32x4_t qload = *reinterpret_cast<const f32x4_t*>(
-      a.q + (static_cast<int64_t>(b) * n_q_heads + hq0 + (qh < nh ? qh : nh - 1)) * kDim +
-      4 * qblk);
-  const f32x4_t qv = qh < nh ? qload : f32x4_t{0.f, 0.f, 0.f, 0.f};
-  const f32x4_t* qpar = reinterpret_cast<const f32x4_t*>(
-      a.quats + static_cast<int64_t>(g) * kQuatFloats + 8 * qblk);
-  const f32x4_t ql = qpar[0], qr = qpar[1];
-  float* part_bg = a.partials + static_cast<int64_t>(bgv) * n_parts * (kHeads * kPart);
-  const int64_t row = kPaged ? 0 : static_cast<int64_t>(b * a.n_kv_heads + g) * a.capacity;
-
-  const int seq0 = a.seq_lens[b];
-  // record index of the new token (its page's slot, or the row position);
-  // -1 when there is no room: the sequence is at capacity, or (paged) the
-  // slot's page is not mapped.  Then nothing is written, the token is not
-  // attended, the capacity flag is raised, and the new-token partial's l
-  // entry carries -1 so that the merge leaves the length as it is.
-  const int64_t rec = !(seq0 >= 0 && seq0 < a.capacity)
-                          ? -1
-                          : (kPaged ? paged_record(a.pages, a.n_kv_heads, b, g, seq0) : row + seq0);
-  const bool written = rec >= 0;
-  const bool attend_new = written && seq0 < a.max_seq_len;
-  if (!written && a.status != nullptr && g == 0 && vg == 0 && tid == 0)
-    atomicOr(a.status, static_cast<int32_t>(IQ_ERR_CAPACITY));
-  // the length the merge counts the live splits of (grids of several rounds)
-  if (a.lens0 != nullptr && g == 0 && vg == 0 && tid == 0) a.lens0[b] = seq0;
-  // waves 4 and 5 compress the new key and value: lane l holds dims 2l,
-  // 2l + 1 and the parameters of SO(4) block l / 2
-  if (wave == 4 || wave == 5) {
-    const void* src = wave == 4 ? a.k_new : a.v_new;
-    const int64_t off = (static_cast<int64_t>(b) * a.n_kv_heads + g) * kDim;
-    float x0, x1;
-    if (a.new_f16) {
-      const uint32_t w =
-          reinterpret_cast<const uint32_t*>(static_cast<const __half*>(src) + off)[lane];
-      x0 = static_cast<float>(__builtin_bit_cast(_Float16, static_cast<uint16_t>(w)));
-      x1 = static_cast<float>(__builtin_bit_cast(_Float16, static_cast<uint16_t>(w >> 16)));
-    } else {
-      const f32x2_t w =
-          reinterpret_cast<const f32x2_t*>(static_cast<const float*>(src) + off)[lane];
-      x0 = w[0];
-      x1 = w[1];
-    }
-    const f32x4_t* qs = reinterpret_cast<const f32x4_t*>(
-        a.quats + static_cast<int64_t>(g) * kQuatFloats + 8 * (lane >> 1));
-    const f32x4_t p0 = qs[0], p1 = qs[1];
-    const float qp[8] = {p0[0], p0[1], p0[2], p0[3], p1[0], p1[1], p1[2], p1[3]};
-    const WaveCode wc = compress_vector_wave<kBits>(x0, x1, qp, a.cb, lane);
-    const int which = wave - 4;
-    if (lane < 4 * kBits) sm.new_rec[which][lane] = wc.word;
-    if (lane == 0) sm.new_scale[which] = wc.scale;
-    if (written && vg == 0) {   // one head group of the KV head writes
-      uint8_t* codes = which == 0 ? a.k_codes : a.v_codes;
-      float* norms = which == 0 ? a.k_norms : a.v_norms;
-      if (lane < 4 * kBits) reinterpret_cast<uint32_t*>(codes + rec * kRB)[lane] = wc.word;
-      if (lane == 0) norms[rec] = wc.scale;
-    }
-  }
-  if (build_lut) build_pair_table(sm, a.cb, tid);
-  f32x4_t y = f32x4_t{0.f, 0.f, 0.f, 0.f};
-  if (tid < kRotThreads) y = rotate_forward(qv, ql, qr, qblk, kInvSqrtDim * a.qscale);
-  lds_barrier();   // new_rec, new_scale, lut
-  if (tid >= kRotThreads) return;
-  // score of the new key for head qh: s^K (q_tilde . C[code]) over this
-  // thread's dims 4 qblk .. +3, summed over the head's 32 lanes (y already
-  // carries the score scale, in log2 units)
-  const int md = 4 * qblk;
-  const f32x4_t k4 = decode_record_dims<kBits>(sm.new_rec[0], sm.lut, md);
-  const f32x4_t v4 = decode_record_dims<kBits>(sm.new_rec[1], sm.lut, md);
-  float dot = y[0] * k4[0] + y[1] * k4[1] + y[2] * k4[2] + y[3] * k4[3];
-  dot += xor_lane<1>(dot);
-  dot += xor_lane<2>(dot);
-  dot += xor_lane<4>(dot);
-  dot += xor_lane<8>(dot);
-  dot += xor_lane<16>(dot);
-  float* pp = part_bg + static_cast<int64_t>(a.n_splits) * (kHeads * kPart) + qh * kPart;
-  if (qblk == 0) {
-    pp[0] = attend_new ? dot * sm.new_scale[0] : -INFINITY;
-    pp[1] = written ? 1.0f : -1.0f;
-  }
-  *reinterpret_cast<f32x4_t*>(pp + 2 + md) = sm.new_scale[1] * v4;
+__device__ __forceinline__ float* new_token_partial(const G8Args<kBits>& a, int bgv) {
+  return a.partials +
+         (static_cast<int64_t>(bgv) * (a.n_splits + 1) + a.n_splits) * (kHeads * kPart);
 }
 
 // One attention work item: split `split` of the row (KV head g, head group
@@ -850,7 +714,8 @@ void decode_g8_kernel(
     const int bgv = b * n_rows + yrow;
     if constexpr (kAppend) {
       if (split == a.n_splits) {
-        append_token<kPaged, kBits, kRope>(sm, a, gsize, g, vg, b, bgv, true);
+        append_token<kPaged, kBits, kRope>(sm, a, gsize, g, vg, b, new_token_partial(a, bgv),
+                                           true);
         return;
       }
     }
@@ -870,8 +735,8 @@ void decode_g8_kernel(
       for (; j < n_app; j += stride) {
         if (!first) lds_barrier();   // the previous item is done with the LDS
         const int b = j / n_rows, yrow = j - b * n_rows;
-        append_token<kPaged, kBits, kRope>(sm, a, gsize, yrow >> vshift, yrow & vshift, b, j,
-                                           false);
+        append_token<kPaged, kBits, kRope>(sm, a, gsize, yrow >> vshift, yrow & vshift, b,
+                                           new_token_partial(a, j), false);
         first = false;
       }
     }
@@ -987,6 +852,21 @@ hipError_t launch_decode_g8(int nb, int64_t n_splits, int64_t split_len, const f
   // attention, and splits past a length take no workgroup.
   constexpr int64_t kCus = 256;
   const bool wide = n_parts * n_rows * batch > kCus;
+  // The span kernel for long lines of work: where the longest rows give each
+  // wave of two workgroups per CU at least 12 batches (3 of its chunks).  With
+  // fewer a wave's last, partial chunk weighs too much: 8 batches per wave
+  // (batch 8 x 4 rows, 16K positions, 4 bits) 30.5 us in fixed splits, 30.2 to
+  // 32.4 in spans; 13 (ragged, at most 25: paged 24 x 8 rows) 40.2 and 39.7; 34
+  // (batch 64 x 2 rows, ragged, at most 64) 84.5 and 68.4.
+  constexpr int64_t kSpanLine = 2 * kCus * kWaves * 12;
+  if (wide && !rope && n_splits > 1 &&
+      batch * n_rows * ((max_seq_len + 15) / 16) >= kSpanLine) {
+    SpanPlan sp;
+    if (span_plan(batch, n_rows, n_splits, max_seq_len, &sp) && sp.workers == 2 * kCus)
+      return launch_decode_span(sp, n_splits, q, k_codes, k_norms, v_codes, v_norms, seq_lens,
+                                capacity, max_seq_len, quats, batch, n_kv_heads, group, scale,
+                                out, partials, append, pages, bits, stream, cb);
+  }
   const size_t lds_pad = wide ? 0 : kOneWorkgroupPadBytes;
   const int64_t n_items = n_parts * n_rows * batch;
   if (n_items > (int64_t{1} << 30)) return hipErrorInvalidValue;   // 32-bit item indices

@@ -1,10 +1,11 @@
 // Device helpers of the group-8 decode kernels (iq_decode_g8.hip, the
-// single-token kernel and the fused step; iq_decode_multi.hip, multi-token
-// decode), and the split merge kernel both launch: constants, the matrix
-// instruction, SDWA field selects, LDS barriers, cross-lane reductions, the
-// forward and inverse rotation in registers, the per-wave staging layout,
-// the cache loads and the decoding of record slices into operand dwords.
-// Internal to the library.
+// single-token kernel and the fused step; iq_decode_span.hip, the same for
+// grids of many work items; iq_decode_multi.hip, multi-token decode):
+// constants, the matrix instruction, SDWA field selects, LDS barriers,
+// cross-lane reductions, the forward and inverse rotation in registers, the
+// per-wave staging layout, the cache loads, the decoding of record slices
+// into operand dwords, the fused step's new token, the span kernel's line of
+// work, and the split merge kernel.  Internal to the library.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -435,6 +436,250 @@ __device__ __forceinline__ void value_pairs(const uint32_t* lut, const uint32_t*
       vb[3][r] = lut_at(lut, nib4x4<1>(hi));
     }
   }
+}
+
+// Writes the fp16 pair table of the codebook (threads 0 .. 2^(2b) - 1).
+template <class Smem, int kBits>
+__device__ __forceinline__ void build_pair_table(Smem& sm, const CodebookB<kBits>& cb, int tid) {
+  constexpr int kLut = 1 << (2 * kBits);
+  if (tid < kLut) {
+    constexpr int kMask = (1 << kBits) - 1;
+    const uint32_t lo =
+        __builtin_bit_cast(uint16_t, static_cast<_Float16>(codebook_level(cb, tid & kMask)));
+    const uint32_t hi =
+        __builtin_bit_cast(uint16_t, static_cast<_Float16>(codebook_level(cb, tid >> kBits)));
+    sm.lut[tid] = lo | (hi << 16);
+  }
+}
+
+// The kernel's arguments, as passed (see decode_g8_kernel).
+template <int kBits>
+struct G8Args {
+  const float* q;
+  uint8_t* k_codes;
+  float* k_norms;
+  uint8_t* v_codes;
+  float* v_norms;
+  const int32_t* seq_lens;
+  const float* quats;
+  float* partials;
+  float* out;
+  int64_t capacity;
+  int max_seq_len, n_kv_heads, n_splits, split_len;
+  float qscale;
+  CodebookB<kBits> cb;
+  const void* k_new;
+  const void* v_new;
+  int new_f16;
+  int32_t* status;
+  PageTable pages;
+  int group, batch;
+  int32_t* lens0;   // fused steps on grids of several rounds: each sequence's length
+};
+
+// ---- the fused step's new token -------------------------------------------
+// For (sequence b, KV head g, head group vg): its key and value are
+// compressed (Alg. 1) and written at position seq_lens[b], and its score and
+// value are published as a partial of their own (m = -inf when the token is
+// not attended: at capacity, or at or past max_seq_len).  No attention work
+// reads the records being written, and seq_lens is advanced by the merge
+// kernel after every workgroup has read it.
+
+// Where the token goes: its record's index (its page's slot, or the row
+// position), -1 when there is no room: the sequence is at capacity, or
+// (paged) the slot's page is not mapped.  Then nothing is written, the token
+// is not attended, the capacity flag is raised, and the partial's l entry
+// carries -1 so that the merge leaves the length as it is.
+struct NewToken {
+  int64_t rec;
+  bool written, attend;
+};
+template <bool kPaged, int kBits>
+__device__ __forceinline__ NewToken new_token(const G8Args<kBits>& a, int g, int b) {
+  const int64_t row = kPaged ? 0 : static_cast<int64_t>(b * a.n_kv_heads + g) * a.capacity;
+  const int seq0 = a.seq_lens[b];
+  const int64_t rec = !(seq0 >= 0 && seq0 < a.capacity)
+                          ? -1
+                          : (kPaged ? paged_record(a.pages, a.n_kv_heads, b, g, seq0) : row + seq0);
+  return NewToken{rec, rec >= 0, rec >= 0 && seq0 < a.max_seq_len};
+}
+// Once per sequence (one thread): the capacity flag, and the sequence's
+// length as read here, for the merge (lens0, grids of several rounds).
+template <int kBits>
+__device__ __forceinline__ void note_new_token(const G8Args<kBits>& a, int b, bool written) {
+  if (!written && a.status != nullptr) atomicOr(a.status, static_cast<int32_t>(IQ_ERR_CAPACITY));
+  if (a.lens0 != nullptr) a.lens0[b] = a.seq_lens[b];
+}
+// One wave compresses the new key (which = 0) or value (1) into
+// sm.new_rec / new_scale and, if `store`, into the cache: lane l holds dims
+// 2l, 2l + 1 and the parameters of SO(4) block l / 2.
+template <int kBits, class Smem>
+__device__ __forceinline__ void compress_new_token(Smem& sm, const G8Args<kBits>& a, int which,
+                                                   int g, int b, int lane, int64_t rec,
+                                                   bool store) {
+  const void* src = which == 0 ? a.k_new : a.v_new;
+  const int64_t off = (static_cast<int64_t>(b) * a.n_kv_heads + g) * kDim;
+  float x0, x1;
+  if (a.new_f16) {
+    const uint32_t w =
+        reinterpret_cast<const uint32_t*>(static_cast<const __half*>(src) + off)[lane];
+    x0 = static_cast<float>(__builtin_bit_cast(_Float16, static_cast<uint16_t>(w)));
+    x1 = static_cast<float>(__builtin_bit_cast(_Float16, static_cast<uint16_t>(w >> 16)));
+  } else {
+    const f32x2_t w = reinterpret_cast<const f32x2_t*>(static_cast<const float*>(src) + off)[lane];
+    x0 = w[0];
+    x1 = w[1];
+  }
+  const f32x4_t* qs = reinterpret_cast<const f32x4_t*>(
+      a.quats + static_cast<int64_t>(g) * kQuatFloats + 8 * (lane >> 1));
+  const f32x4_t p0 = qs[0], p1 = qs[1];
+  const float qp[8] = {p0[0], p0[1], p0[2], p0[3], p1[0], p1[1], p1[2], p1[3]};
+  const WaveCode wc = compress_vector_wave<kBits>(x0, x1, qp, a.cb, lane);
+  if (lane < 4 * kBits) sm.new_rec[which][lane] = wc.word;
+  if (lane == 0) sm.new_scale[which] = wc.scale;
+  if (store) {
+    uint8_t* codes = which == 0 ? a.k_codes : a.v_codes;
+    float* norms = which == 0 ? a.k_norms : a.v_norms;
+    if (lane < 4 * kBits)
+      reinterpret_cast<uint32_t*>(codes + rec * record_bytes<kBits>())[lane] = wc.word;
+    if (lane == 0) norms[rec] = wc.scale;
+  }
+}
+// The new token's partial: thread (head qh, SO(4) block qblk) with its 4 dims
+// y of the rotated query (carrying the score scale, in log2 units); the score
+// is s^K (q_tilde . C[code]) summed over the head's 32 lanes.
+template <int kBits, class Smem>
+__device__ __forceinline__ void publish_new_token(const Smem& sm, f32x4_t y, const NewToken& tok,
+                                                  float* part_new, int qh, int qblk) {
+  const int md = 4 * qblk;
+  const f32x4_t k4 = decode_record_dims<kBits>(sm.new_rec[0], sm.lut, md);
+  const f32x4_t v4 = decode_record_dims<kBits>(sm.new_rec[1], sm.lut, md);
+  float dot = y[0] * k4[0] + y[1] * k4[1] + y[2] * k4[2] + y[3] * k4[3];
+  dot += xor_lane<1>(dot);
+  dot += xor_lane<2>(dot);
+  dot += xor_lane<4>(dot);
+  dot += xor_lane<8>(dot);
+  dot += xor_lane<16>(dot);
+  float* pp = part_new + qh * kPart;
+  if (qblk == 0) {
+    pp[0] = tok.attend ? dot * sm.new_scale[0] : -INFINITY;
+    pp[1] = tok.written ? 1.0f : -1.0f;
+  }
+  *reinterpret_cast<f32x4_t*>(pp + 2 + md) = sm.new_scale[1] * v4;
+}
+
+// A workgroup that only appends: waves 0..3 rotate the query, waves 4 and 5
+// compress.
+template <bool kPaged, int kBits, bool kRope, class Smem>
+__device__ __forceinline__ void append_token(Smem& sm, const G8Args<kBits>& a,
+                                             int gsize, int g, int vg, int b, float* part_new,
+                                             bool build_lut) {
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));   // recomputed per item (see attend_split)
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lane = tid & 63;
+  const int n_q_heads = a.n_kv_heads * gsize;
+  const int hq0 = g * gsize + kHeads * vg;
+  const int nh = gsize - kHeads * vg < kHeads ? gsize - kHeads * vg : kHeads;
+  const int qh = (tid >> 5) & 7, qblk = tid & 31;
+  const f32x4_t qload = *reinterpret_cast<const f32x4_t*>(
+      a.q + (static_cast<int64_t>(b) * n_q_heads + hq0 + (qh < nh ? qh : nh - 1)) * kDim +
+      4 * qblk);
+  const f32x4_t qv = qh < nh ? qload : f32x4_t{0.f, 0.f, 0.f, 0.f};
+  const f32x4_t* qpar = reinterpret_cast<const f32x4_t*>(
+      a.quats + static_cast<int64_t>(g) * kQuatFloats + 8 * qblk);
+  const f32x4_t ql = qpar[0], qr = qpar[1];
+  const NewToken tok = new_token<kPaged>(a, g, b);
+  if (g == 0 && vg == 0 && tid == 0) note_new_token(a, b, tok.written);
+  if (wave == 4 || wave == 5)   // one head group of the KV head writes
+    compress_new_token(sm, a, wave - 4, g, b, lane, tok.rec, tok.written && vg == 0);
+  if (build_lut) build_pair_table(sm, a.cb, tid);
+  f32x4_t y = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  if (tid < kRotThreads) y = rotate_forward(qv, ql, qr, qblk, kInvSqrtDim * a.qscale);
+  lds_barrier();   // new_rec, new_scale, lut
+  if (tid < kRotThreads) publish_new_token<kBits>(sm, y, tok, part_new, qh, qblk);
+}
+
+// ---- the line of work of the span kernel (iq_decode_span.hip) ---------------
+// The rows of every sequence (KV head x head group) one after another, each
+// kRowBatches + ceil(len / 16) batches long (len: the length clamped to [0,
+// max_seq_len]), cut into equal runs, one per workgroup.  The kernel and the
+// merge compute the same line from the same lengths.
+
+// What a row costs besides its batches, in batches: the end of one span and
+// the start of the next.  (Steps of batch 64 x 2 rows / paged 24 x 8 rows: 4
+// batches 74 / 47 us, 12: 74 / 43, 20: 73 / 41, 30: 73 / 40, 48: 73 / 40.)
+constexpr int kRowBatches = 30;
+// Sequences the line can hold (lengths are summed 64 at a time by every wave
+// of the kernel and of its merge).
+constexpr int kSpanMaxBatch = 512;
+// Shortest run (one batch per wave).
+constexpr int kSpanMinRun = 8;
+
+struct SpanLine {
+  int total;   // batches
+  int run;     // batches per workgroup
+};
+
+__device__ __forceinline__ int span_length(int s, int max_seq_len) {
+  return s < 0 ? 0 : (s > max_seq_len ? max_seq_len : s);
+}
+// Length on the line of each row of a sequence.
+__device__ __forceinline__ int span_width(int len) { return kRowBatches + ((len + 15) >> 4); }
+
+// Inclusive prefix sum over the wave's lanes: shifts within the rows of 16
+// lanes, then the rows' sums carried on (all vector instructions).
+__device__ __forceinline__ int wave_scan(int x) {
+  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xF, 0xF, true);    // row_shr:1
+  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xF, 0xF, true);    // row_shr:2
+  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xF, 0xF, true);    // row_shr:4
+  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xF, 0xF, true);    // row_shr:8
+  x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xA, 0xF, false);   // row_bcast:15, rows 1, 3
+  x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xC, 0xF, false);   // row_bcast:31, rows 2, 3
+  return x;
+}
+
+// The line, and where the rows of sequence `before` start on it (0 if there
+// is none); the same in every lane.
+__device__ __forceinline__ SpanLine span_line(const int32_t* __restrict__ lens, int batch,
+                                              int n_rows, int max_seq_len, int workers, int lane,
+                                              int before, int* start) {
+  int total = 0;
+  *start = 0;
+  for (int c0 = 0; c0 < batch; c0 += 64) {
+    const int w =
+        c0 + lane < batch ? n_rows * span_width(span_length(lens[c0 + lane], max_seq_len)) : 0;
+    const int incl = wave_scan(w);
+    if (before >= c0 && before < c0 + 64)
+      *start = total + __builtin_amdgcn_readlane(incl - w, before - c0);
+    total += __builtin_amdgcn_readlane(incl, 63);
+  }
+  const int run = (total + workers - 1) / workers;
+  return SpanLine{total, run < kSpanMinRun ? kSpanMinRun : run};
+}
+
+// The sequence whose rows hold batch x (< total) of the line, and where they
+// start; the same in every lane.
+__device__ __forceinline__ void span_find(const int32_t* __restrict__ lens, int batch, int n_rows,
+                                          int max_seq_len, int lane, int x, int* seq,
+                                          int* start) {
+  int base = 0;
+  *seq = batch;
+  for (int c0 = 0; c0 < batch; c0 += 64) {
+    const int w =
+        c0 + lane < batch ? n_rows * span_width(span_length(lens[c0 + lane], max_seq_len)) : 0;
+    const int incl = wave_scan(w);
+    const int sum = __builtin_amdgcn_readlane(incl, 63);
+    if (x < base + sum) {
+      // the lanes whose inclusive sum is at most x - base come before it
+      const int i = __builtin_popcountll(__ballot(incl <= x - base));
+      *seq = c0 + i;
+      *start = base + __builtin_amdgcn_readlane(incl - w, i);
+      return;
+    }
+    base += sum;
+  }
+  *start = base;
 }
 
 // Merge of the split partials of one (sequence b, query head h): grid

@@ -174,6 +174,24 @@ hipError_t launch_decode_g8(int nb, int64_t n_splits, int64_t split_len, const f
                             hipStream_t stream, const iq_codebook_t* cb = nullptr,
                             const RopeKeys* rope = nullptr);
 
+// The span kernel (iq_decode_span.hip): launch_decode_g8's work for grids of
+// many work items, and for rows that are not whole batches of 16 positions.
+// workers: its workgroups; by_rows: they take whole rows instead of runs.
+struct SpanPlan {
+  int workers;
+  bool by_rows;
+};
+// n_rows, n_splits as in g8_plan; false if the call does not fit the kernel.
+bool span_plan(int64_t batch, int64_t n_rows, int64_t n_splits, int64_t max_seq_len,
+               SpanPlan* plan);
+hipError_t launch_decode_span(const SpanPlan& plan, int64_t n_splits, const float* q,
+                              uint8_t* k_codes, float* k_norms, uint8_t* v_codes, float* v_norms,
+                              int32_t* seq_lens, int64_t capacity, int64_t max_seq_len,
+                              const float* quats, int64_t batch, int64_t n_kv_heads,
+                              int64_t group, float scale, float* out, float* partials,
+                              const StepAppend* append, const PageTable* pages, int bits,
+                              hipStream_t stream, const iq_codebook_t* cb);
+
 // Multi-token decode on records of `bits` bits (group 8): n_tok (2..4)
 // query tokens per sequence, q / out [batch][n_tok][8 n_kv_heads][128]; the
 // plan is g8_plan's, partials [batch][n_kv_heads][n_parts][n_tok][8][130]

@@ -1,0 +1,115 @@
+"""GPU parity of the span kernel (decode and fused step on long lines of work:
+rows of every sequence cut into equal runs, one per workgroup) against the
+oracle: lengths around every chunk, wave and batch edge, empty sequences, runs
+that hold several rows and rows that cross runs, 2-, 3- and 4-bit records,
+pages, head groups other than 8, and a single long sequence among empty ones."""
+
+import numpy as np
+import pytest
+import torch
+
+from oracle import attention as oatt
+from oracle import codebook as ocb
+from oracle import compress as ocz
+from oracle import rotation as orot
+from paper_2608_08081_amd import api
+from tests.parity import row_rel_err
+
+pytestmark = pytest.mark.gpu
+DEV = torch.device("cuda:0")
+
+# Scores carry the query as fp16 hi + lo pairs: off by at most 2^-21 of |q||k|
+# scale, below 64 in log2 units here, so weights by ln 2 * 64 * 2^-21 = 2.1e-5;
+# weights themselves are cut after 20 bits.
+RTOL = 5e-5
+
+EDGES = [0, 1, 15, 16, 17, 63, 64, 65, 127, 128, 129, 511, 512, 513, 640, 1023, 1024, 1025]
+
+
+def _records(rng, shape, bits):
+    """Random records (every code equally often) and scales."""
+    return (rng.integers(0, 256, size=(*shape, 16 * bits), dtype=np.uint8),
+            (14.0 * np.exp(0.35 * rng.standard_normal(shape))).astype(np.float32))
+
+
+def _dev(x):
+    return torch.from_numpy(np.ascontiguousarray(x)).to(DEV)
+
+
+def _lengths(kind, batch, cap):
+    if kind == "edges":
+        return [EDGES[i % len(EDGES)] if i % 2 else (977 * i) % (cap - 1) for i in range(batch)]
+    if kind == "full":
+        return [cap - 1] * batch
+    return [cap - 1 if i == batch // 2 else 0 for i in range(batch)]   # "one"
+
+
+@pytest.mark.parametrize("bits,group,kind,page,step", [
+    (3, 8, "edges", 0, True), (3, 8, "edges", 0, False), (3, 8, "one", 0, True),
+    (3, 8, "one", 0, False), (2, 8, "edges", 0, True), (4, 8, "edges", 0, True),
+    (3, 4, "edges", 16, True), (3, 16, "edges", 64, False), (3, 5, "full", 0, True),
+])
+def test_span_against_oracle(bits, group, kind, page, step):
+    hkv, cap = 2, 2112
+    rows = hkv * (2 if group > 8 else 1)
+    batch = -(-49152 // (rows * (cap // 16)))   # the shortest line that takes the kernel
+    seq = _lengths(kind, batch, cap)
+    print(f"[span] bits={bits} group={group} {kind} page={page} step={step} batch={batch}",
+          flush=True)
+    rng = np.random.default_rng([5, bits, group, page])
+    kc, kn = _records(rng, (batch, hkv, cap), bits)
+    vc, vn = _records(rng, (batch, hkv, cap), bits)
+    quats = orot.make_quaternions(77, hkv)
+    levels, thr = ocb.isoquant_codebook(128, bits)
+    q = rng.standard_normal((batch, hkv * group, 128), dtype=np.float32)
+    k_new = rng.standard_normal((batch, hkv, 128), dtype=np.float32)
+    v_new = rng.standard_normal((batch, hkv, 128), dtype=np.float32)
+    gk, gkn, gv, gvn = kc.copy(), kn.copy(), vc.copy(), vn.copy()
+    for i, n in enumerate(seq):   # a read of a position that is not attended shows up
+        gkn[i, :, n:] = np.nan
+        gvn[i, :, n:] = np.nan
+    lens = _dev(np.asarray(seq, np.int32))
+    ws = api.alloc_workspace(batch, hkv * group, hkv, cap, DEV)
+    ws.fill_(0x44)
+    if page:
+        per = cap // page
+        table = rng.permutation(batch * per).astype(np.int32).reshape(batch, per)
+        cache = {}
+        for nm, x in (("k_codes", gk), ("k_norms", gkn), ("v_codes", gv), ("v_norms", gvn)):
+            pool = np.empty((batch * per, hkv, page, *x.shape[3:]), x.dtype)
+            pool[table.reshape(-1)] = np.moveaxis(
+                x[:, :, :per * page].reshape(batch, hkv, per, page, *x.shape[3:]), 2, 1).reshape(
+                    batch * per, hkv, page, *x.shape[3:])
+            cache[nm] = _dev(pool)
+        tab = _dev(table)
+        assert max(seq) < per * page
+    else:
+        cache = {"k_codes": _dev(gk), "k_norms": _dev(gkn), "v_codes": _dev(gv),
+                 "v_norms": _dev(gvn)}
+    args = (cache["k_codes"], cache["k_norms"], cache["v_codes"], cache["v_norms"], lens,
+            _dev(quats))
+    if step and page:
+        out = api.iq_decode_step_paged(_dev(q), _dev(k_new), _dev(v_new), cache, tab, lens,
+                                       _dev(quats), workspace=ws)
+    elif step:
+        out = api.iq_decode_step_bits(_dev(q), _dev(k_new), _dev(v_new), *args, workspace=ws,
+                                      bits=bits)
+    elif page:
+        out = api.iq_decode_attention_paged(_dev(q), cache, tab, lens, _dev(quats), workspace=ws)
+    else:
+        out = api.iq_decode_attention_bits(_dev(q), *args, workspace=ws, bits=bits)
+    torch.cuda.synchronize()
+    if step:
+        assert lens.cpu().tolist() == [n + 1 for n in seq]
+        rots = orot.rotation_matrices(quats)
+        pk, nk, *_ = ocz.compress_kv(k_new[:, :, None], rots, thr)
+        pv, nv, *_ = ocz.compress_kv(v_new[:, :, None], rots, thr)
+        for i, n in enumerate(seq):
+            kc[i, :, n], kn[i, :, n] = pk[i, :, 0], nk[i, :, 0]
+            vc[i, :, n], vn[i, :, n] = pv[i, :, 0], nv[i, :, 0]
+    ref = oatt.decode_fused(q, kc, kn, vc, vn, [n + step for n in seq], quats, levels)
+    got = out.cpu().numpy()
+    assert np.all(np.isfinite(got))
+    err = row_rel_err(got, ref)
+    print(f"[span] max row rel err {err.max():.3e}", flush=True)
+    assert err.max() <= RTOL
