@@ -244,11 +244,12 @@ iq_status iq_decode_workspace_init(void* workspace, size_t workspace_bytes,
  * workspace : device, >= iq_decode_workspace_bytes(...) bytes, 256-byte
  *             aligned, contents ignored on entry.  Calls that share a
  *             workspace must not overlap in time.
- * n_q_heads / n_kv_heads must be an integer <= 16.  Caches whose capacity
- * is a multiple of 16 (>= 16, capacity * 48 < 2^31) with 16-byte aligned
- * scale arrays run on the matrix cores (query heads in groups of 8 per KV
- * head; batch and n_kv_heads * ceil(group / 8) <= 65535), other caches on a
- * vector-unit path with the same results to rounding.
+ * n_q_heads / n_kv_heads must be an integer <= 16.  Caches with
+ * capacity * 48 < 2^31 run on the matrix cores (query heads in groups of 8
+ * per KV head; batch and n_kv_heads * ceil(group / 8) <= 65535; batch <= 512
+ * where the capacity is not a multiple of 16 or a scale array is not 16-byte
+ * aligned and rows are split), other caches on a vector-unit path with the
+ * same results to rounding.
  */
 iq_status iq_decode_attention(const float* q,
                               const uint8_t* k_codes, const float* k_norms,

@@ -1,5 +1,6 @@
 // Decode attention on the packed 3-bit cache (App. A; Table 2; Sec. 3.4)
-// for gfx950, generic path (any group size G <= 16).
+// for gfx950: the split plan, the choice of kernel, and the generic path (any
+// group size G <= 16, any row length and alignment).
 //
 // Two launches:
 //  1. split kernel, one workgroup per (sequence, KV head, split of positions):
@@ -316,6 +317,23 @@ hipError_t launch_decode(const DecodePlan& plan, const float* q, uint8_t* k_code
                             k_norms, v_codes, v_norms, seq_lens, capacity, max_seq_len, quats,
                             batch, n_kv_heads, group, scale, out, parts, append, nullptr, 3,
                             stream, cb);
+  }
+  // Rows that are not whole batches of 16 positions, or scales that are not
+  // 16-byte aligned (a cache sized prompt + output): the span kernel, whose
+  // loads end with the row and take scales one by one.  One sequence of 8700
+  // positions in rows of 9192, 4 KV heads: 105 us per step on the vector-unit
+  // kernels below, 24 here; 16 ragged sequences of up to 6000: 243 and 24.
+  // Those kernels keep what the span kernel cannot address: rows over 2 GiB,
+  // more than 65535 sequences or rows, and (several splits per row) more than
+  // kSpanMaxBatch sequences.
+  SpanPlan sp;
+  const int64_t n_rows = n_kv_heads * ((group + 7) / 8);
+  if (plan.g8_batches > 0 && row32 && grid_ok &&
+      span_plan(batch, n_rows, plan.g8_splits, max_seq_len, &sp)) {
+    float* parts = reinterpret_cast<float*>(static_cast<char*>(workspace) + plan.ticket_bytes);
+    return launch_decode_span(sp, plan.g8_splits, q, k_codes, k_norms, v_codes, v_norms, seq_lens,
+                              capacity, max_seq_len, quats, batch, n_kv_heads, group, scale, out,
+                              parts, append, nullptr, 3, stream, cb);
   }
   if (append) {
     // generic path of the fused step: the append kernel, then attention

@@ -113,3 +113,61 @@ def test_span_against_oracle(bits, group, kind, page, step):
     err = row_rel_err(got, ref)
     print(f"[span] max row rel err {err.max():.3e}", flush=True)
     assert err.max() <= RTOL
+
+
+@pytest.mark.parametrize("batch,hkv,group,cap,step,shift", [
+    (1, 1, 1, 1, True, 0), (1, 1, 1, 5, False, 0), (1, 4, 8, 17, True, 0), (3, 2, 8, 131, True, 0),
+    (2, 2, 4, 777, False, 0), (5, 2, 16, 1031, True, 0), (300, 2, 8, 103, True, 0),
+    (300, 2, 8, 103, False, 0), (2, 4, 8, 9191, True, 0), (7, 2, 5, 1025, True, 1),
+    (3, 2, 8, 1040, True, 1), (1, 2, 8, 641, True, 3),
+])
+def test_rows_of_any_length(batch, hkv, group, cap, step, shift):
+    """Rows that are not whole batches of 16 positions (whose last loads end with the row; the
+    buffers hold nothing past the last row) and scales that are only 4-byte aligned (shift)."""
+    print(f"[rows] batch={batch} hkv={hkv} group={group} cap={cap} step={step}", flush=True)
+    rng = np.random.default_rng([6, batch, cap])
+    kc, kn = _records(rng, (batch, hkv, cap), 3)
+    vc, vn = _records(rng, (batch, hkv, cap), 3)
+    seq = [(cap - step, 0, cap // 2, cap - step, 1 % cap)[i % 5] if i < 5 else (31 * i) % cap
+           for i in range(batch)]
+    seq = [min(n, cap - step) for n in seq]
+    quats = orot.make_quaternions(78, hkv)
+    levels, thr = ocb.isoquant_codebook(128, 3)
+    q = rng.standard_normal((batch, hkv * group, 128), dtype=np.float32)
+    k_new = rng.standard_normal((batch, hkv, 128), dtype=np.float32).astype(np.float16)
+    v_new = rng.standard_normal((batch, hkv, 128), dtype=np.float32).astype(np.float16)
+
+    def scales(x):
+        x = x.copy()
+        for i, n in enumerate(seq):
+            x[i, :, n:] = np.nan
+        buf = torch.empty(x.size + shift, dtype=torch.float32, device=DEV)
+        view = buf[shift:].view(x.shape)
+        view.copy_(torch.from_numpy(x))
+        return view
+
+    lens = _dev(np.asarray(seq, np.int32))
+    args = (_dev(kc), scales(kn), _dev(vc), scales(vn), lens, _dev(quats))
+    ws = api.alloc_workspace(batch, hkv * group, hkv, cap, DEV)
+    ws.fill_(0x44)
+    if step:
+        out = api.iq_decode_step(_dev(q), _dev(k_new), _dev(v_new), *args, workspace=ws)
+    else:
+        out = api.iq_decode_attention(_dev(q), *args, workspace=ws)
+    torch.cuda.synchronize()
+    if step:
+        assert lens.cpu().tolist() == [n + 1 for n in seq]
+        rots = orot.rotation_matrices(quats)
+        pk, nk, *_ = ocz.compress_kv(k_new[:, :, None], rots, thr)
+        pv, nv, *_ = ocz.compress_kv(v_new[:, :, None], rots, thr)
+        for i, n in enumerate(seq):
+            kc[i, :, n], kn[i, :, n] = pk[i, :, 0], nk[i, :, 0]
+            vc[i, :, n], vn[i, :, n] = pv[i, :, 0], nv[i, :, 0]
+        assert np.array_equal(args[0].cpu().numpy(), kc)   # nothing else was written
+        assert np.array_equal(args[2].cpu().numpy(), vc)
+    ref = oatt.decode_fused(q, kc, kn, vc, vn, [n + step for n in seq], quats, levels)
+    got = out.cpu().numpy()
+    assert np.all(np.isfinite(got))
+    err = row_rel_err(got, ref)
+    print(f"[rows] max row rel err {err.max():.3e}", flush=True)
+    assert err.max() <= RTOL
