@@ -5,9 +5,9 @@
 // workgroup (4 waves) takes 128 consecutive tokens of one (K|V, sequence, KV
 // head); it first builds the head's 32 block matrices M_i H_4 in LDS (2 KB),
 // which the lanes then read as 16-byte rows (two addresses per read, one per
-// half: LDS broadcasts).  Half a vector per lane keeps about 100 registers
-// per lane, so five waves share a SIMD and the vector-ALU work of one wave
-// runs while the others wait on memory.
+// half: LDS broadcasts).  Half a vector per lane takes 89 registers (fp16
+// input, 3 bits), so five waves share a SIMD and the vector-ALU work of one
+// wave runs while the others wait on memory.
 //
 // Per vector:
 //   s^2  = sum x_i^2 in fp64 (products of fp16/fp32 inputs are exact in fp64),
@@ -25,8 +25,9 @@
 //          comparing R x / s against t_j, and saves 128 multiplies).  The
 //          codebook is symmetric (t_{6-j} = -t_j, t_3 = 0), so the code is
 //          4 + m for y >= 0 and 3 - m = (4 + m) ^ 7 for y < 0, where
-//          m = #{k = 1..3 : |y| >= T_k} comes from a two-step search; the
-//          two rules differ only when |y| equals a threshold exactly;
+//          m = #{k = 1..3 : |y| >= T_k}, read off the signs of y and |y| - T_k
+//          (see push_code); the two rules differ only when |y| equals a
+//          threshold exactly;
 //   pack = 3-bit codes into 12 words; codes 0..63 fill words 0..5 (lower
 //          lane) and codes 64..127 words 6..11 (upper lane), each lane
 //          storing its 24 bytes (Step 4).
@@ -77,59 +78,6 @@ __device__ __forceinline__ void load_half(const float* src, float (&x)[kHalfDim]
   }
 }
 
-// Code of y against the scaled positive thresholds T1 < T2 < T3 of a
-// symmetric codebook (see the file comment), already shifted to bit `off`
-// of its record word: ((4 + m) ^ (y < 0 ? 7 : 0)) << off, built from three
-// selects of shifted constants.
-__device__ __forceinline__ uint32_t quantize_sym(float y, float t1, float t2, float t3, int off) {
-  const float a = fabsf(y);
-  const bool b1 = a >= t2;
-  const bool b0 = a >= (b1 ? t3 : t1);
-  const uint32_t hi = b1 ? (6u << off) : (4u << off);
-  const uint32_t lo = b0 ? (1u << off) : 0u;
-  const uint32_t flip = y >= 0.f ? 0u : (7u << off);
-  return (hi | lo) ^ flip;
-}
-
-// The same rule for b = 2 and b = 4 (h = 2^(b-1) levels per sign, positive
-// thresholds t[0] < ... < t[h-2]): code (h + m) ^ (y < 0 ? 2h - 1 : 0) with
-// m = #{k : |y| >= t[k]}.  Codes of 2 and 4 bits never
-// straddle a 32-bit word.
-template <int kBits>
-__device__ __forceinline__ uint32_t quantize_sym_b(float y, const float (&t)[(1 << (kBits - 1)) - 1],
-                                                   int off) {
-  constexpr uint32_t h = 1u << (kBits - 1);
-  const float a = fabsf(y);
-  uint32_t m;
-  if constexpr (kBits == 2) {
-    m = a >= t[0] ? 1u : 0u;
-  } else {
-    static_assert(kBits == 4, "2 or 4 bits");
-    // a plain count: a select tree over 7 thresholds, interleaved across
-    // coordinates, more than doubles the register footprint
-    m = 0u;
-#pragma unroll
-    for (int k = 0; k < 7; ++k) m += a >= t[k] ? 1u : 0u;
-  }
-  const uint32_t flip = y >= 0.f ? 0u : (2 * h - 1);
-  return ((h + m) ^ flip) << off;
-}
-
-// OR the code of coordinate i of a half (bits 3i .. 3i+2 of the half
-// record) into w.
-__device__ __forceinline__ void put_code_sym(uint32_t (&w)[kRecordWords / 2], int i, float y,
-                                             float t1, float t2, float t3) {
-  const int bit = 3 * i;
-  const int word = bit >> 5, off = bit & 31;
-  if (off <= 29) {
-    w[word] |= quantize_sym(y, t1, t2, t3, off);
-  } else {
-    const uint32_t c = quantize_sym(y, t1, t2, t3, 0);
-    w[word] |= c << off;
-    w[word + 1] |= c >> (32 - off);
-  }
-}
-
 // x[i] += x_partner[i] * sg for i = i0 .. i0 + 7, the partner lane being
 // lane ^ 1: one multiply-add per value whose first operand is read from the
 // partner lane (DPP quad permutation [1, 0, 3, 2]).  Written out because the
@@ -151,6 +99,84 @@ __device__ __forceinline__ void cross_butterfly8(float (&x)[kDim / 2], int i0, f
       : "+v"(x[i0]), "+v"(x[i0 + 1]), "+v"(x[i0 + 2]), "+v"(x[i0 + 3]), "+v"(x[i0 + 4]),
         "+v"(x[i0 + 5]), "+v"(x[i0 + 6]), "+v"(x[i0 + 7])
       : "v"(sg));
+}
+
+// ---- the quantizer in sign bits --------------------------------------------
+// A coordinate's code is read off the signs of floats: y itself, and d_k =
+// |y| - T_k (negative exactly where |y| < T_k: a float difference has the sign
+// of the exact one, and +0 on a tie).  With c_k = [|y| >= T_k], m = c_1 +
+// c_2 + ... has the bits m_0 = c_1 ^ c_2 ^ c_3 ..., m_1 = c_2 ^ c_4 ^ c_6, m_2
+// = c_4, each the inverted sign of an exclusive or of an odd number of d_k.
+// So every code bit is a sign, shifted into the record word by one funnel
+// shift, and code = (h + m) ^ (y < 0 ? 2h - 1 : 0) is the complement of the
+// collected signs with the sign of y applied to the lower bits, which is done
+// on whole words at the end.  No compares or selects: these go through
+// condition masks, whose readers wait on gfx950 (168 s_nop per half vector
+// were left after scheduling).  The kernel is bound by vector instructions, of
+// which a half vector now has 1321 instead of 1475 (and 89 registers instead
+// of 127): 4 x 8 x 32768 keys and values in fp16 181 -> 168 us, 3.8 TB/s.
+// Word w takes one more bit, the sign of `bits`.
+__device__ __forceinline__ uint32_t push_sign(uint32_t w, uint32_t bits) {
+  return __builtin_amdgcn_alignbit(w, bits, 31);
+}
+
+// a ^ b ^ c, one instruction.
+__device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
+  uint32_t r;
+  asm("v_bitop3_b32 %0, %1, %2, %3 bitop3:0x96" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+  return r;
+}
+
+// The code bits of one coordinate (index i of its half), its highest bit first:
+// coordinates are pushed from the last to the first, so that code i ends at
+// bits b i .. b i + b - 1.
+template <int kBits>
+__device__ __forceinline__ void push_code(uint32_t (&w)[2 * kBits], int i, float y,
+                                          const float (&t)[(1 << (kBits - 1)) - 1]) {
+  constexpr int n = (1 << (kBits - 1)) - 1;
+  uint32_t d[n];
+#pragma unroll
+  for (int k = 0; k < n; ++k) d[k] = __builtin_bit_cast(uint32_t, fabsf(y) - t[k]);
+  const int bit = kBits * i;
+  auto push = [&](int j, uint32_t bits) { w[(bit + j) >> 5] = push_sign(w[(bit + j) >> 5], bits); };
+  push(kBits - 1, __builtin_bit_cast(uint32_t, y));
+  if constexpr (kBits == 2) {
+    push(0, d[0]);
+  } else if constexpr (kBits == 3) {
+    push(1, d[1]);
+    push(0, xor3(d[0], d[1], d[2]));
+  } else {
+    static_assert(kBits == 4, "2, 3 or 4 bits");
+    push(2, d[3]);
+    push(1, xor3(d[1], d[3], d[5]));
+    push(0, xor3(xor3(d[0], d[1], d[2]), xor3(d[3], d[4], d[5]), d[6]));
+  }
+}
+
+// The half record of the collected signs: the lower bits of each code take its
+// sign (bit b - 1), then everything is inverted.
+template <int kBits>
+__device__ __forceinline__ void finish_codes(uint32_t (&w)[2 * kBits]) {
+  constexpr int n = 2 * kBits;
+  uint32_t neg[n + 1];
+#pragma unroll
+  for (int k = 0; k < n; ++k) {
+    // bits b - 1, 2b - 1, ... of the bit string (3 bits: the pattern moves on
+    // by 32 mod 3 from word to word)
+    const uint32_t mask = kBits == 2   ? 0xAAAAAAAAu
+                          : kBits == 4 ? 0x88888888u
+                                       : (k % 3 == 0 ? 0x24924924u
+                                                     : (k % 3 == 1 ? 0x49249249u : 0x92492492u));
+    neg[k] = w[k] & mask;
+  }
+  neg[n] = 0u;
+#pragma unroll
+  for (int k = 0; k < n; ++k) {
+    uint32_t x = w[k];
+#pragma unroll
+    for (int j = 1; j < kBits; ++j) x ^= __builtin_amdgcn_alignbit(neg[k + 1], neg[k], j);
+    w[k] = ~x;
+  }
 }
 
 // Compress one half of a vector (Algorithm 1) and write its half of the
@@ -187,7 +213,19 @@ __device__ __forceinline__ void compress_half(const T* __restrict__ src, const f
   // Positive thresholds in the unnormalized domain: t_j * s * sqrt(128).  A
   // zero vector keeps the plain thresholds, so its all-zero y maps to the
   // first non-negative level.
-  const double sc = ss > 0.0 ? s * 11.313708498984760390 : 1.0;   // sqrt(128)
+  double sc = ss > 0.0 ? s * 11.313708498984760390 : 1.0;   // sqrt(128)
+  // fp32 inputs near the top of the range: scaled down by an exact power of
+  // two, so that no sum overflows (|y| and every partial sum are below 12 s)
+  // and y - T is a number
+  if constexpr (sizeof(T) == 4) {
+    const bool large = ss >= 0x1p200;
+    if (__any(large)) {
+      const float f = large ? 0x1p-64f : 1.0f;
+      sc *= static_cast<double>(f);
+#pragma unroll
+      for (int i = 0; i < kHalfDim; ++i) x[i] *= f;
+    }
+  }
   float tp[kHalf - 1];
 #pragma unroll
   for (int j = 0; j < kHalf - 1; ++j) {
@@ -220,21 +258,22 @@ __device__ __forceinline__ void compress_half(const T* __restrict__ src, const f
 #pragma unroll
   for (int i = 0; i < kWords; ++i) w[i] = 0u;
 #pragma unroll
-  for (int blk = 0; blk < kNumBlocks / 2; ++blk) {
+  for (int blk = kNumBlocks / 2 - 1; blk >= 0; --blk) {
     const float z0 = x[4 * blk], z1 = x[4 * blk + 1], z2 = x[4 * blk + 2], z3 = x[4 * blk + 3];
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
+    for (int r = 3; r >= 0; --r) {
       const f32x4_t m = mt[4 * blk + r];
-      const float y = m[0] * z0 + m[1] * z1 + m[2] * z2 + m[3] * z3;
-      const int i = 4 * blk + r;
-      if constexpr (kBits == 3) {
-        put_code_sym(w, i, y, tp[0], tp[1], tp[2]);
-      } else {
-        const int bit = kBits * i;
-        w[bit >> 5] |= quantize_sym_b<kBits>(y, tp, bit & 31);
-      }
+      // (from +0: an all-zero block gives +0, not -0)
+      float y = __builtin_fmaf(m[1], z1, 0.f);
+      y = __builtin_fmaf(m[0], z0, y);
+      y = __builtin_fmaf(m[2], z2, y);
+      y = __builtin_fmaf(m[3], z3, y);
+      // (fp32 inputs: products may underflow to -0, which counts as 0)
+      if constexpr (sizeof(T) == 4) y += 0.f;
+      push_code<kBits>(w, 4 * blk + r, y, tp);
     }
   }
+  finish_codes<kBits>(w);
   if (!finite) {
 #pragma unroll
     for (int i = 0; i < kWords; ++i) w[i] = 0u;
