@@ -150,6 +150,31 @@ def lib() -> ctypes.CDLL:
     return _lib
 
 
+# functions of the native argument checks, in the order _bind.bind takes them
+_BOUND = ("iq_compress_kv", "iq_compress_kv_bits", "iq_decode_attention",
+          "iq_decode_attention_bits", "iq_decode_step", "iq_decode_step_bits",
+          "iq_decode_attention_paged", "iq_decode_step_paged", "iq_decode_attention_multi",
+          "iq_decode_attention_multi_bits", "iq_decode_step_multi", "iq_decode_attention_rope",
+          "iq_dequantize_kv")
+_native = None
+
+
+def native():
+    """The native argument checks (module _bind), tied to lib()'s functions.
+    Raises if it is not built."""
+    global _native
+    if _native is None:
+        handle = lib()
+        try:
+            from . import _bind
+        except ImportError as e:
+            raise RuntimeError("paper_2608_08081_amd/_bind.so is missing or does not load: build "
+                               "it with __graft_entry__.build()") from e
+        _bind.bind(*(ctypes.cast(getattr(handle, n), ctypes.c_void_p).value for n in _BOUND))
+        _native = _bind
+    return _native
+
+
 def check(fn: str, status: int) -> None:
     if status != IQ_OK:
         raise IsoQuantError(fn, status)

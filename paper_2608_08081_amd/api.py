@@ -4,6 +4,10 @@ Argument marshalling only: tensors are checked for device, dtype, shape and
 contiguity (the C library cannot see tensor extents), then their device
 pointers and the current HIP stream are handed to the C ABI.  All
 compression and attention arithmetic runs in the library's HIP kernels.
+
+The calls of a serving loop (every buffer given) are checked and made by the
+native module _bind; whatever it leaves (a wrong argument, a missing buffer, a
+tensor subclass) takes the general path here, with the same checks.
 """
 
 from __future__ import annotations
@@ -216,6 +220,12 @@ def iq_compress_kv_cb(k, v, quats, codebook, k_codes=None, k_norms=None, v_codes
 
 def _compress(k, v, quats, k_codes, k_norms, v_codes, v_norms, dst_offset, bits,
               codebook=None):
+    if codebook is None:
+        st = _lib.native().compress(k, v, quats, k_codes, k_norms, v_codes, v_norms, dst_offset,
+                                    bits)
+        if st is not None:
+            _lib.check("iq_compress_kv" if bits == 3 else "iq_compress_kv_bits", st)
+            return
     src = k if k is not None else v
     if src is None:
         raise ValueError("k and v are both None")
@@ -321,6 +331,12 @@ def iq_decode_attention_cb(q, k_codes, k_norms, v_codes, v_norms, seq_lens, quat
 
 def _decode(q, k_codes, k_norms, v_codes, v_norms, seq_lens, quats, out, workspace,
             max_seq_len, softmax_scale, bits, codebook=None):
+    if codebook is None:
+        st = _lib.native().decode(q, k_codes, k_norms, v_codes, v_norms, seq_lens, quats, out,
+                                  workspace, max_seq_len, softmax_scale, bits)
+        if st is not None:
+            _lib.check("iq_decode_attention" if bits == 3 else "iq_decode_attention_bits", st)
+            return out
     if q.dim() != 3 or q.shape[-1] != HEAD_DIM:
         raise ValueError("q must be [batch][n_q_heads][128]")
     b, hq, _ = q.shape
@@ -364,6 +380,11 @@ def iq_decode_attention_rope(q, q_rope, k_codes, k_norms, k_rope, v_codes, v_nor
     """Decode with the content / RoPE sub-block split: q [B][H_q][128] and
     q_rope [B][H_q][64] fp32; the compressed content cache; k_rope fp16
     [B][1 or H_kv][cap][64] (stored as given).  Returns out [B][H_q][128]."""
+    st = _lib.native().rope(q, q_rope, k_rope, k_codes, k_norms, v_codes, v_norms, seq_lens,
+                            quats, out, workspace, max_seq_len, softmax_scale)
+    if st is not None:
+        _lib.check("iq_decode_attention_rope", st)
+        return out
     if q.dim() != 3 or q.shape[-1] != HEAD_DIM:
         raise ValueError("q must be [batch][n_q_heads][128]")
     b, hq, _ = q.shape
@@ -409,6 +430,12 @@ def iq_decode_attention_multi(q, k_codes, k_norms, v_codes, v_norms, seq_lens, q
     sequence, the last T of its seq_lens[b] cached positions; token t attends
     positions before seq_lens[b] - T + 1 + t) on b-bit records
     ([B][H_kv][cap][16 b]).  Returns out [B][T][H_q][128]."""
+    st = _lib.native().multi(q, k_codes, k_norms, v_codes, v_norms, seq_lens, quats, out,
+                             workspace, max_seq_len, softmax_scale, bits)
+    if st is not None:
+        _lib.check("iq_decode_attention_multi" if bits == 3 else
+                   "iq_decode_attention_multi_bits", st)
+        return out
     if q.dim() != 4 or q.shape[-1] != HEAD_DIM:
         raise ValueError("q must be [batch][n_tokens][n_q_heads][128]")
     b, t, hq, _ = q.shape
@@ -455,6 +482,11 @@ def iq_decode_step_multi(q, k_new, v_new, k_codes, k_norms, v_codes, v_norms, se
     b-bit records, attend q [B][T][H_q][128] (token t: the cached positions
     and new positions 0 .. t) and advance seq_lens by T in place.  Returns
     out [B][T][H_q][128] fp32 (original space)."""
+    st = _lib.native().step_multi(q, k_new, v_new, k_codes, k_norms, v_codes, v_norms, seq_lens,
+                                  quats, out, workspace, max_seq_len, softmax_scale, status, bits)
+    if st is not None:
+        _lib.check("iq_decode_step_multi", st)
+        return out
     if q.dim() != 4 or q.shape[-1] != HEAD_DIM:
         raise ValueError("q must be [batch][n_tokens][n_q_heads][128]")
     b, t, hq, _ = q.shape
@@ -568,6 +600,12 @@ def iq_decode_step_cb(q, k_new, v_new, k_codes, k_norms, v_codes, v_norms, seq_l
 
 def _step(q, k_new, v_new, k_codes, k_norms, v_codes, v_norms, seq_lens, quats, out, workspace,
           max_seq_len, softmax_scale, status, bits, codebook=None):
+    if codebook is None:
+        st = _lib.native().step(q, k_new, v_new, k_codes, k_norms, v_codes, v_norms, seq_lens,
+                                quats, out, workspace, max_seq_len, softmax_scale, status, bits)
+        if st is not None:
+            _lib.check("iq_decode_step" if bits == 3 else "iq_decode_step_bits", st)
+            return out
     b, hq, hkv, cap = _step_shapes(q, k_new, v_new, k_codes, k_norms, v_codes, v_norms,
                                    seq_lens, quats, status, bits)
     dev = q.device
@@ -658,6 +696,12 @@ def iq_compress_kv_paged(k, v, quats, pool, block_tables, dst_offset: int = 0):
 def iq_decode_attention_paged(q, pool, block_tables, seq_lens, quats, out=None,
                               workspace=None, max_seq_len=None, softmax_scale: float = 0.0):
     """iq_decode_attention on page pools; q [B][8 H_kv][128]."""
+    st = _lib.native().decode_paged(q, pool.get("k_codes"), pool.get("k_norms"),
+                                    pool.get("v_codes"), pool.get("v_norms"), block_tables,
+                                    seq_lens, quats, out, workspace, max_seq_len, softmax_scale)
+    if st is not None:
+        _lib.check("iq_decode_attention_paged", st)
+        return out
     b, hq, _ = q.shape
     dev = q.device
     _require(q, "q", torch.float32, (b, hq, HEAD_DIM), dev)
@@ -685,6 +729,13 @@ def iq_decode_step_paged(q, k_new, v_new, pool, block_tables, seq_lens, quats, o
                          status=None):
     """iq_decode_step on page pools: the new token goes to logical position
     seq_lens[b] (its page must be mapped in block_tables)."""
+    st = _lib.native().step_paged(q, k_new, v_new, pool.get("k_codes"), pool.get("k_norms"),
+                                  pool.get("v_codes"), pool.get("v_norms"), block_tables,
+                                  seq_lens, quats, out, workspace, max_seq_len, softmax_scale,
+                                  status)
+    if st is not None:
+        _lib.check("iq_decode_step_paged", st)
+        return out
     b, hq, _ = q.shape
     dev = q.device
     _require(q, "q", torch.float32, (b, hq, HEAD_DIM), dev)
@@ -762,6 +813,12 @@ def iq_dequantize_kv(k_codes, k_norms, v_codes, v_norms, quats, n_tokens=None,
     original-space vectors [B][H_kv][n_tokens][128] of out_dtype (fp16 or
     fp32).  Either side may be None.  With seq_lens, tokens at or past a
     sequence's length are not written.  Returns (k_out, v_out)."""
+    if codebook is None and getattr(k_out, "dtype", None) is out_dtype:
+        st = _lib.native().dequantize(k_codes, k_norms, v_codes, v_norms, quats, n_tokens,
+                                      src_offset, seq_lens, k_out, v_out)
+        if st is not None:
+            _lib.check("iq_dequantize_kv", st)
+            return k_out, v_out
     ref = k_codes if k_codes is not None else v_codes
     if ref is None or ref.dim() != 4:
         raise ValueError("codes must be [batch][n_kv_heads][capacity][48]")

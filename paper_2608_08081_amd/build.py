@@ -1,4 +1,5 @@
-"""Build libisoquant.so (HIP, gfx950) in-tree with hipcc.
+"""Build libisoquant.so (HIP, gfx950) with hipcc and the Python binding's
+native argument checks (_bind.so) in-tree.
 
 Usage: ``python -m paper_2608_08081_amd.build`` or ``build()`` from Python.
 Every call compiles from source; the result is written next to this file.
@@ -46,6 +47,38 @@ HOST_SANITIZE_FLAGS = ["-Xarch_host", "-fsanitize=address", "-Xarch_host",
                        "-Xarch_host", "-fno-omit-frame-pointer", "-g"]
 
 
+BIND_SOURCE = "iq_bind.cpp"
+BIND_NAME = "_bind.so"
+
+
+def build_bind(verbose: bool = False) -> str:
+    """Compile the binding's native argument checks (module _bind, host code
+    against torch's and Python's headers) next to this file."""
+    import sysconfig
+
+    import torch
+    tdir = os.path.dirname(torch.__file__)
+    rocm = os.path.dirname(os.path.dirname(os.path.realpath(_hipcc())))
+    out = os.path.join(PKG, BIND_NAME)
+    tmp = out + ".tmp"
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared",
+           "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           "-I", INCLUDE, "-isystem", os.path.join(tdir, "include"),
+           "-isystem", os.path.join(tdir, "include", "torch", "csrc", "api", "include"),
+           "-isystem", os.path.join(rocm, "include"), "-isystem", sysconfig.get_paths()["include"],
+           "-Wall", os.path.join(CSRC, BIND_SOURCE), "-o", tmp,
+           "-L", os.path.join(tdir, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10_hip", "-lc10",
+           f"-Wl,-rpath,{os.path.join(tdir, 'lib')}"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"{BIND_SOURCE}:\n{r.stdout}\n{r.stderr}")
+    os.replace(tmp, out)
+    return out
+
+
 def build(verbose: bool = False, extra_flags: list[str] | None = None,
           host_sanitize: bool = False) -> str:
     """Compile every source for gfx950 and link the shared library.
@@ -72,8 +105,11 @@ def build(verbose: bool = False, extra_flags: list[str] | None = None,
             print(r.stderr, file=sys.stderr)
         return obj
 
-    with ThreadPoolExecutor(max_workers=len(SOURCES)) as ex:
+    with ThreadPoolExecutor(max_workers=len(SOURCES) + 1) as ex:
+        bind = None if host_sanitize else ex.submit(build_bind, verbose)
         objs = list(ex.map(compile_one, SOURCES))
+        if bind is not None:
+            bind.result()
     out = os.path.join(bdir, LIB_NAME) if host_sanitize else os.path.join(PKG, LIB_NAME)
     tmp = out + ".tmp"
     link_extra = ["-fsanitize=address,undefined", "-shared-libsan"] if host_sanitize else []

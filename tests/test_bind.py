@@ -1,0 +1,98 @@
+"""The native argument checks of the binding: what they leave to the general
+path (CPU), and that both paths give the same results and errors (GPU)."""
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2608_08081_amd import _lib, api
+
+
+def test_everything_else_goes_to_the_general_path():
+    nat = _lib.native()
+    t = torch.zeros(1, 16, 128)
+    for fn, n in (("compress", 9), ("decode", 12), ("step", 15), ("decode_paged", 12),
+                  ("step_paged", 15), ("multi", 12), ("step_multi", 15), ("rope", 13),
+                  ("dequantize", 10)):
+        f = getattr(nat, fn)
+        assert f(*[None] * n) is None            # nothing given
+        assert f(*[t] * n) is None               # host tensors
+        assert f(*[object()] * n) is None
+        assert f() is None and f(t) is None      # too few
+
+
+def _case(b=2, hkv=2, group=8, cap=64, dev="cuda:0"):
+    g = torch.Generator(device=dev).manual_seed(3)
+    c = api.alloc_cache(b, hkv, cap, dev)
+    quats = api.iq_make_rotation(9, hkv).to(dev)
+    x = torch.randn((b, hkv, 40, 128), generator=g, device=dev).half()
+    api.iq_compress_kv(x, x.flip(2).contiguous(), quats, c["k_codes"], c["k_norms"], c["v_codes"],
+                       c["v_norms"])
+    c["seq_lens"].fill_(40)
+    q = torch.randn((b, hkv * group, 128), generator=g, device=dev)
+    k = torch.randn((b, hkv, 128), generator=g, device=dev).half()
+    return c, quats, q, k, torch.empty_like(q), api.alloc_workspace(b, hkv * group, hkv, cap, dev)
+
+
+@pytest.mark.gpu
+def test_both_paths_agree(monkeypatch):
+    c, quats, q, k, out, ws = _case()
+    rows = (c["k_codes"], c["k_norms"], c["v_codes"], c["v_norms"], c["seq_lens"], quats)
+
+    class General:   # the native module that never calls
+        def __getattr__(self, name):
+            return lambda *a: None
+
+    got = []
+    for general in (False, True):
+        if general:
+            monkeypatch.setattr(_lib, "native", lambda: General())
+        c["seq_lens"].fill_(40)
+        a = api.iq_decode_attention(q, *rows, out=out, workspace=ws).clone()
+        s = api.iq_decode_step(q, k, k, *rows, out=out, workspace=ws).clone()
+        d = api.iq_dequantize_kv(*rows[:4], quats, k_out=torch.empty((2, 2, 64, 128), device="cuda:0",
+                                                                      dtype=torch.float16),
+                                 v_out=torch.empty((2, 2, 64, 128), device="cuda:0",
+                                                   dtype=torch.float16))
+        got.append((a, s, *d, c["seq_lens"].clone(), c["k_codes"].clone()))
+    for x, y in zip(*got):
+        assert torch.equal(x, y)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("wrong,error", [
+    ({"q": lambda t: t.half()}, TypeError), ({"q": lambda t: t[:, :, :64]}, ValueError),
+    ({"k": lambda t: t.bfloat16()}, TypeError), ({"k": lambda t: t.cpu()}, ValueError),
+    ({"out": lambda t: t.transpose(0, 1)}, ValueError), ({"ws": lambda t: t.float()}, ValueError),
+    ({"ws": lambda t: t[:256]}, _lib.IsoQuantError), ({"quats": lambda t: t[:1]}, ValueError),
+    ({"lens": lambda t: t.long()}, TypeError), ({"most": lambda m: 65}, _lib.IsoQuantError),
+])
+def test_wrong_arguments_raise_as_before(wrong, error):
+    c, quats, q, k, out, ws = _case()
+    a = dict(q=q, k=k, quats=quats, out=out, ws=ws, lens=c["seq_lens"], most=None)
+    before = c["k_codes"].clone()
+    for name, f in wrong.items():
+        a[name] = f(a[name])
+    with pytest.raises(error):
+        api.iq_decode_step(a["q"], a["k"], a["k"], c["k_codes"], c["k_norms"], c["v_codes"],
+                           c["v_norms"], a["lens"], a["quats"], out=a["out"], workspace=a["ws"],
+                           max_seq_len=a["most"])
+    assert torch.equal(before, c["k_codes"])
+
+
+@pytest.mark.gpu
+def test_calls_go_to_the_current_stream():
+    c, quats, q, k, out, ws = _case()
+    args = (q, c["k_codes"], c["k_norms"], c["v_codes"], c["v_norms"], c["seq_lens"], quats)
+    want = api.iq_decode_attention(*args, out=out, workspace=ws).clone()
+    torch.cuda.synchronize()
+    side, out2 = torch.cuda.Stream(), torch.zeros_like(out)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        api.iq_decode_attention(*args, out=out2, workspace=ws)
+    assert not np.any(out2.cpu().numpy())   # captured, not run
+    for _ in range(3):
+        out2.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out2, want)
