@@ -858,14 +858,14 @@ hipError_t launch_decode_g8(int nb, int64_t n_splits, int64_t split_len, const f
   // (batch 8 x 4 rows, 16K positions, 4 bits) 30.5 us in fixed splits, 30.2 to
   // 32.4 in spans; 13 (ragged, at most 25: paged 24 x 8 rows) 40.2 and 39.7; 34
   // (batch 64 x 2 rows, ragged, at most 64) 84.5 and 68.4.
-  constexpr int64_t kSpanLine = 2 * kCus * kWaves * 12;
-  if (wide && !rope && n_splits > 1 &&
-      batch * n_rows * ((max_seq_len + 15) / 16) >= kSpanLine) {
+  const int64_t span_wgs = (rope ? 1 : 2) * kCus;
+  const int64_t span_line = span_wgs * kWaves * (rope ? 8 : 12);
+  if (wide && n_splits > 1 && batch * n_rows * ((max_seq_len + 15) / 16) >= span_line) {
     SpanPlan sp;
-    if (span_plan(batch, n_rows, n_splits, max_seq_len, &sp) && sp.workers == 2 * kCus)
+    if (span_plan(batch, n_rows, n_splits, max_seq_len, span_wgs, &sp) && sp.workers == span_wgs)
       return launch_decode_span(sp, n_splits, q, k_codes, k_norms, v_codes, v_norms, seq_lens,
                                 capacity, max_seq_len, quats, batch, n_kv_heads, group, scale,
-                                out, partials, append, pages, bits, stream, cb);
+                                out, partials, append, pages, bits, stream, cb, rope);
   }
   const size_t lds_pad = wide ? 0 : kOneWorkgroupPadBytes;
   const int64_t n_items = n_parts * n_rows * batch;

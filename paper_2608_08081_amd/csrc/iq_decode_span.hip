@@ -57,10 +57,11 @@ struct SpanStage {
 };
 
 // LDS of the kernel, the pair table first (see G8Smem).
-template <int kBits>
+template <int kBits, bool kRope>
 struct SpanSmem {
   uint32_t lut[1 << (2 * kBits)];
   uint32_t qop[2][kHeads][kQRowWords];
+  uint32_t qop_r[kRope ? 2 : 1][kHeads][kRope ? kRopeRowWords : 1];   // positional operands
   int qexp[kHeads];
   float wave_ml[kWaves][2][kHeads];
   uint32_t new_rec[2][4 * kBits];   // the row's new token: its records,
@@ -139,21 +140,23 @@ __device__ __forceinline__ void window_pairs(const uint32_t* lut, const uint32_t
 // share of the head's sum of weights; unit: the power of two at or below the
 // largest value scale so far (its bits), the outputs being in units of unit /
 // 2^14.
-template <int kBits>
+template <int kBits, bool kRope>
 struct SpanState {
   float m, l;
   uint32_t unit;
   f32x4_t o[4];
   uint32_t kw[kSpanBatches][kBits], vw[kSpanBatches][4];
   float ks, vs;   // lane j: position j of the chunk
+  u32x4_t rk[kRope ? kSpanBatches : 1][2];   // positional keys (see attend_wave)
 };
 
 // One chunk: the batches held in s.kw / s.vw / s.ks / s.vs, nvalid positions
 // (kFull: all of them).  next_keys / next_values issue the next chunk's loads
 // into the same registers as soon as these are free.
-template <bool kFull, int kBits, class NextKeys, class NextValues>
-__device__ __forceinline__ void span_chunk(SpanState<kBits>& s, SpanStage& st,
-                                           const u32x4_t (&qb)[4], const uint32_t* lut, int lane,
+template <bool kFull, int kBits, bool kRope, class NextKeys, class NextValues>
+__device__ __forceinline__ void span_chunk(SpanState<kBits, kRope>& s, SpanStage& st,
+                                           const u32x4_t (&qb)[4], const u32x4_t (&qbr)[2],
+                                           const uint32_t* lut, int lane,
                                            int col, int grp, int nvalid, uint32_t vsh, float qdown,
                                            NextKeys next_keys, NextValues next_values) {
   constexpr int NB = kSpanBatches;
@@ -182,9 +185,20 @@ __device__ __forceinline__ void span_chunk(SpanState<kBits>& s, SpanStage& st,
     f32x4_t acc = f32x4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int kb = 0; kb < 4; ++kb) acc = mfma(a[kb], qb[kb], acc);
+    const f32x4_t ks = *reinterpret_cast<const f32x4_t*>(&st.ks[16 * i + 4 * grp]);
+    f32x4_t x;
+    if constexpr (kRope) {
+      f32x4_t accr = f32x4_t{0.f, 0.f, 0.f, 0.f};
+      accr = mfma(s.rk[i][0], qbr[0], accr);
+      accr = mfma(s.rk[i][1], qbr[1], accr);
+      x = acc * ks + accr;
 #pragma unroll
-    for (int r = 0; r < 4; ++r) acc[r] += xor_lane<8>(acc[r]);
-    const f32x4_t x = acc * *reinterpret_cast<const f32x4_t*>(&st.ks[16 * i + 4 * grp]);
+      for (int r = 0; r < 4; ++r) x[r] += xor_lane<8>(x[r]);
+    } else {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) acc[r] += xor_lane<8>(acc[r]);
+      x = acc * ks;
+    }
     f32x2_t xs = upper ? f32x2_t{x[2], x[3]} : f32x2_t{x[0], x[1]};
     if (!kFull && 16 * i + 16 > nvalid) {
 #pragma unroll
@@ -269,9 +283,13 @@ __device__ __forceinline__ void span_chunk(SpanState<kBits>& s, SpanStage& st,
 // the others attend, and its score is taken when the span ends, so that the
 // append adds a fraction of a microsecond to the span (as a work item of its
 // own it took 4 us of the workgroup, 32 to 48 batches' time).
-template <bool kAppend, bool kPaged, int kBits>
-__device__ __forceinline__ void attend_span(SpanSmem<kBits>& sm, const G8Args<kBits>& a, int gsize,
-                                            int g, int vg, int b, int a0, int a1, int len,
+//
+// kRope: the content / RoPE sub-block split of decode_g8_kernel (decode only,
+// contiguous 3-bit caches; the append's three arguments carry k_rope, q_rope
+// and rope_shared).
+template <bool kAppend, bool kPaged, int kBits, bool kRope>
+__device__ __forceinline__ void attend_span(SpanSmem<kBits, kRope>& sm, const G8Args<kBits>& a,
+                                            int gsize, int g, int vg, int b, int a0, int a1, int len,
                                             float* part, bool append, float* part_new) {
   constexpr int NB = kSpanBatches;
   constexpr int kRB = record_bytes<kBits>();
@@ -288,6 +306,14 @@ __device__ __forceinline__ void attend_span(SpanSmem<kBits>& sm, const G8Args<kB
       a.q + (static_cast<int64_t>(b) * n_q_heads + hq0 + (qh < nh ? qh : nh - 1)) * kDim +
       4 * qblk);
   const f32x4_t qv = qh < nh ? qload : f32x4_t{0.f, 0.f, 0.f, 0.f};
+  f32x4_t qrv = f32x4_t{0.f, 0.f, 0.f, 0.f};   // positional dims 4 qblk .. (qblk < 16)
+  if constexpr (kRope) {
+    const f32x4_t t = *reinterpret_cast<const f32x4_t*>(
+        static_cast<const float*>(a.v_new) +
+        (static_cast<int64_t>(b) * n_q_heads + hq0 + (qh < nh ? qh : nh - 1)) * kRopeDim +
+        4 * (qblk & 15));
+    qrv = (qh < nh && qblk < 16) ? t : f32x4_t{0.f, 0.f, 0.f, 0.f};
+  }
   const f32x4_t* qpar = reinterpret_cast<const f32x4_t*>(
       a.quats + static_cast<int64_t>(g) * kQuatFloats + 8 * qblk);
   const f32x4_t ql = qpar[0], qr = qpar[1];
@@ -345,7 +371,7 @@ __device__ __forceinline__ void attend_span(SpanSmem<kBits>& sm, const G8Args<kB
   };
   const int koff = col * kRB + 4 * kBits * grp;
   int64_t dlt[NB];
-  SpanState<kBits> s;
+  SpanState<kBits, kRope> s;
   const int cap = static_cast<int>(a.capacity);
   // records of the batch at t: lane (t, gk) takes dwords b gk .. b gk + b - 1
   // of record t, through a buffer descriptor that ends with the row (lanes
@@ -381,12 +407,27 @@ __device__ __forceinline__ void attend_span(SpanSmem<kBits>& sm, const G8Args<kB
       return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rsrc, 4 * lane, 0, 0));
     }
   };
+  // positional keys: lane (t, gk) takes dims 8 gk .. + 7 and 32 + 8 gk .. + 7
+  // of position t (16-byte loads; the capacity is a multiple of 16)
+  const uint16_t* rp = nullptr;
+  if constexpr (kRope)
+    rp = static_cast<const uint16_t*>(a.k_new) +
+         (static_cast<int64_t>(b) * (a.new_f16 ? 1 : a.n_kv_heads) + (a.new_f16 ? 0 : g)) *
+             a.capacity * kRopeDim;
   auto load_k = [&](int at) {
     s.ks = load_scale(kn, at);
     s.vs = load_scale(vn, at);
 #pragma unroll
-    for (int i = 0; i < NB; ++i)
-      load_records(kc, dlt[i], at + 16 * i < last16 ? at + 16 * i : last16, s.kw[i]);
+    for (int i = 0; i < NB; ++i) {
+      const int t = at + 16 * i < last16 ? at + 16 * i : last16;
+      load_records(kc, dlt[i], t, s.kw[i]);
+      if constexpr (kRope) {
+        const u32x4_t* src =
+            reinterpret_cast<const u32x4_t*>(rp + static_cast<int64_t>(t + col) * kRopeDim);
+        s.rk[i][0] = src[grp];
+        s.rk[i][1] = src[4 + grp];
+      }
+    }
     __builtin_amdgcn_sched_barrier(0);
   };
   // value windows: lane (u, gk) takes, of records 4 gk + r, the dword that
@@ -416,8 +457,14 @@ __device__ __forceinline__ void attend_span(SpanSmem<kBits>& sm, const G8Args<kB
   // ---- while the loads fly: the rotated query as operands in LDS ----------
   if (tid < kRotThreads) {
     const f32x4_t y = rotate_forward(qv, ql, qr, qblk, kInvSqrtDim * a.qscale);
-    const float am =
-        group32_max(fmaxf(fmaxf(fabsf(y[0]), fabsf(y[1])), fmaxf(fabsf(y[2]), fabsf(y[3]))));
+    // the positional part, scaled like the scores, shares the head's operand
+    // scale
+    const f32x4_t yr = qrv * a.qscale;
+    float amx = fmaxf(fmaxf(fabsf(y[0]), fabsf(y[1])), fmaxf(fabsf(y[2]), fabsf(y[3])));
+    if constexpr (kRope)
+      amx = fmaxf(amx,
+                  fmaxf(fmaxf(fabsf(yr[0]), fabsf(yr[1])), fmaxf(fabsf(yr[2]), fabsf(yr[3]))));
+    const float am = group32_max(amx);
     int qexp = 0;
     if (am > 0.f) {
       int e = 0;
@@ -426,18 +473,25 @@ __device__ __forceinline__ void attend_span(SpanSmem<kBits>& sm, const G8Args<kB
       qexp = qexp > 100 ? 100 : (qexp < -100 ? -100 : qexp);
     }
     const float qup = ldexpf(1.0f, qexp);
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const float x0 = y[2 * j] * qup, x1 = y[2 * j + 1] * qup;
+    // fp16 hi and lo parts of a pair, as operand dwords
+    auto split_pair = [&](float x0, float x1, uint32_t& hi, uint32_t& lo) {
       const _Float16 h0 = static_cast<_Float16>(x0), h1 = static_cast<_Float16>(x1);
       const _Float16 l0 = static_cast<_Float16>(x0 - static_cast<float>(h0));
       const _Float16 l1 = static_cast<_Float16>(x1 - static_cast<float>(h1));
-      sm.qop[0][qh][2 * qblk + j] =
-          static_cast<uint32_t>(__builtin_bit_cast(uint16_t, h0)) |
-          (static_cast<uint32_t>(__builtin_bit_cast(uint16_t, h1)) << 16);
-      sm.qop[1][qh][2 * qblk + j] =
-          static_cast<uint32_t>(__builtin_bit_cast(uint16_t, l0)) |
-          (static_cast<uint32_t>(__builtin_bit_cast(uint16_t, l1)) << 16);
+      hi = static_cast<uint32_t>(__builtin_bit_cast(uint16_t, h0)) |
+           (static_cast<uint32_t>(__builtin_bit_cast(uint16_t, h1)) << 16);
+      lo = static_cast<uint32_t>(__builtin_bit_cast(uint16_t, l0)) |
+           (static_cast<uint32_t>(__builtin_bit_cast(uint16_t, l1)) << 16);
+    };
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      split_pair(y[2 * j] * qup, y[2 * j + 1] * qup, sm.qop[0][qh][2 * qblk + j],
+                 sm.qop[1][qh][2 * qblk + j]);
+      if constexpr (kRope) {
+        if (qblk < 16)
+          split_pair(yr[2 * j] * qup, yr[2 * j + 1] * qup, sm.qop_r[0][qh][2 * qblk + j],
+                     sm.qop_r[1][qh][2 * qblk + j]);
+      }
     }
     if (qblk == 0) sm.qexp[qh] = qexp;
     if (kAppend && append) sm.new_q[qh][qblk] = y;
@@ -457,6 +511,12 @@ __device__ __forceinline__ void attend_span(SpanSmem<kBits>& sm, const G8Args<kB
 #pragma unroll
   for (int kb = 0; kb < 4; ++kb)
     qb[kb] = *reinterpret_cast<const u32x4_t*>(&sm.qop[col >> 3][col & 7][16 * grp + 4 * kb]);
+  u32x4_t qbr[2];
+  if constexpr (kRope) {
+#pragma unroll
+    for (int m = 0; m < 2; ++m)
+      qbr[m] = *reinterpret_cast<const u32x4_t*>(&sm.qop_r[col >> 3][col & 7][16 * m + 4 * grp]);
+  }
   const float qdown = ldexpf(1.0f, -sm.qexp[col & 7]);
   s.m = -INFINITY;
   s.l = 0.f;
@@ -471,8 +531,8 @@ __device__ __forceinline__ void attend_span(SpanSmem<kBits>& sm, const G8Args<kB
     left -= 16 * NB;
     if constexpr (kPaged)
       if (p - page_t == 64 * 16) load_pages(p);
-    span_chunk<true, kBits>(
-        s, st, qb, sm.lut, lane, col, grp, 16 * NB, vsh, qdown,
+    span_chunk<true, kBits, kRope>(
+        s, st, qb, qbr, sm.lut, lane, col, grp, 16 * NB, vsh, qdown,
         [&] {
           page_deltas(p, dlt);
           load_k(p);
@@ -480,8 +540,8 @@ __device__ __forceinline__ void attend_span(SpanSmem<kBits>& sm, const G8Args<kB
         [&] { load_v(p); });
   }
   if (left > 0)
-    span_chunk<false, kBits>(
-        s, st, qb, sm.lut, lane, col, grp, left, vsh, qdown, [] {}, [] {});
+    span_chunk<false, kBits, kRope>(
+        s, st, qb, qbr, sm.lut, lane, col, grp, left, vsh, qdown, [] {}, [] {});
 
   // ---- merge the 8 waves in LDS, as in attend_split -------------------------
   const float l = cols_sum(s.l + xor_lane<8>(s.l));
@@ -537,8 +597,11 @@ __device__ __forceinline__ void attend_span(SpanSmem<kBits>& sm, const G8Args<kB
 //
 // by_rows (workspaces of one slot per row, i.e. short sequences): the
 // workgroups take whole rows w, w + gridDim.x, ... instead, row r in slot r.
-template <bool kAppend, bool kPaged, int kBits>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4)))
+//
+// kRope: 32 more registers of positional keys per wave, so one workgroup per
+// CU.
+template <bool kAppend, bool kPaged, int kBits, bool kRope>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kRope ? 2 : 4)))
 void decode_span_kernel(
     const float* __restrict__ q, uint8_t* __restrict__ k_codes, float* __restrict__ k_norms,
     uint8_t* __restrict__ v_codes, float* __restrict__ v_norms,
@@ -551,7 +614,8 @@ void decode_span_kernel(
                         quats,    partials, nullptr, capacity, max_seq_len, n_kv_heads,
                         n_splits, 0,       qscale,  cb,       k_new,       v_new,
                         new_f16,  status,  pages,   group,    batch,       lens0};
-  __shared__ __attribute__((aligned(16))) SpanSmem<kBits> sm;
+  static_assert(!kRope || (!kAppend && !kPaged && kBits == 3), "decode of 3-bit rows");
+  __shared__ __attribute__((aligned(16))) SpanSmem<kBits, kRope> sm;
   const int vshift = group > kHeads ? 1 : 0;
   const int n_rows = n_kv_heads << vshift;
   const int wg = static_cast<int>(blockIdx.x), n_wg = static_cast<int>(gridDim.x);
@@ -588,7 +652,7 @@ void decode_span_kernel(
     }
     if (append || a1 > a0) {
       if (!first) lds_barrier();   // the previous span is done with the LDS
-      attend_span<kAppend, kPaged, kBits>(
+      attend_span<kAppend, kPaged, kBits, kRope>(
           sm, a, group, y >> vshift, y & vshift, b, a0, a1, len,
           partials + (static_cast<int64_t>(by_rows ? 0 : wg) + r) * (kHeads * kPart), append,
           partials + (static_cast<int64_t>(batch) * n_rows * n_splits + r) * (kHeads * kPart));
@@ -736,22 +800,22 @@ __global__ __launch_bounds__(kThreads) void merge_span_kernel(
 // How the span kernel runs a call.  Runs need a slot for every span (runs +
 // rows - 1 of them) in the n_splits slots per row of the workspace, lengths
 // that every wave can sum (at most kSpanMaxBatch) and a line of 32-bit
-// length; with one slot per row the workgroups take whole rows.  At most two
-// workgroups per CU.  false: neither is possible.
+// length; with one slot per row the workgroups take whole rows.  At most
+// `workgroups` of them (two per CU, one with positional keys).  false: neither
+// is possible.
 bool span_plan(int64_t batch, int64_t n_rows, int64_t n_splits, int64_t max_seq_len,
-               SpanPlan* plan) {
-  constexpr int64_t kWorkers = 512;
+               int64_t workgroups, SpanPlan* plan) {
   const int64_t rows = batch * n_rows;
   if (rows * (n_splits + 1) > (int64_t{1} << 30)) return false;   // slots: 32-bit indices
   if (n_splits == 1) {
-    *plan = SpanPlan{static_cast<int>(rows < kWorkers ? rows : kWorkers), true};
+    *plan = SpanPlan{static_cast<int>(rows < workgroups ? rows : workgroups), true};
     return true;
   }
   if (batch > kSpanMaxBatch ||
-      rows * ((max_seq_len + 15) / 16 + kRowBatches) + kWorkers > 0x3fffffff)
+      rows * ((max_seq_len + 15) / 16 + kRowBatches) + workgroups > 0x3fffffff)
     return false;
   const int64_t most = rows * (n_splits - 1) + 1;
-  *plan = SpanPlan{static_cast<int>(most < kWorkers ? most : kWorkers), false};
+  *plan = SpanPlan{static_cast<int>(most < workgroups ? most : workgroups), false};
   return true;
 }
 
@@ -761,21 +825,22 @@ hipError_t launch_decode_span(const SpanPlan& plan, int64_t n_splits, const floa
                               const float* quats, int64_t batch, int64_t n_kv_heads,
                               int64_t group, float scale, float* out, float* partials,
                               const StepAppend* append, const PageTable* pages, int bits,
-                              hipStream_t stream, const iq_codebook_t* cb) {
+                              hipStream_t stream, const iq_codebook_t* cb, const RopeKeys* rope) {
   const int64_t n_rows = n_kv_heads * ((group + kHeads - 1) / kHeads);
   const dim3 grid(static_cast<unsigned>(plan.workers)), block(kThreads);
   const float qscale = scale * kLog2e;
-  const void* k_new = append ? append->k_new : nullptr;
-  const void* v_new = append ? append->v_new : nullptr;
-  const int new_f16 = append ? append->f16 : 0;
+  // the positional split passes its arguments in the append's three
+  const void* k_new = append ? append->k_new : (rope ? rope->k_rope : nullptr);
+  const void* v_new = append ? append->v_new : (rope ? rope->q_rope : nullptr);
+  const int new_f16 = append ? append->f16 : (rope ? rope->shared : 0);
   int32_t* status = append ? append->status : nullptr;
   const PageTable pt = pages ? *pages : PageTable{nullptr, 0, 4, 1};
   int32_t* const lens0 =
       append ? reinterpret_cast<int32_t*>(reinterpret_cast<char*>(partials) +
                                           g8_partial_region_bytes(batch, n_rows, n_splits))
              : nullptr;
-#define IQ_LAUNCH_SPAN(APP_, PAGED_, BITS_)                                                     \
-  hipLaunchKernelGGL((decode_span_kernel<APP_, PAGED_, BITS_>), grid, block, 0, stream, q,       \
+#define IQ_LAUNCH_SPAN(APP_, PAGED_, BITS_, ROPE_)                                              \
+  hipLaunchKernelGGL((decode_span_kernel<APP_, PAGED_, BITS_, ROPE_>), grid, block, 0, stream, q, \
                      k_codes, k_norms, v_codes, v_norms, seq_lens, quats, partials, capacity,   \
                      static_cast<int>(max_seq_len), static_cast<int>(n_kv_heads),               \
                      static_cast<int>(n_splits), qscale, codebook_for<BITS_>(cb), k_new, v_new, \
@@ -783,15 +848,17 @@ hipError_t launch_decode_span(const SpanPlan& plan, int64_t n_splits, const floa
                      lens0, plan.by_rows ? 1 : 0)
 #define IQ_LAUNCH_SPAN_A(APP_)                        \
   if (pages) {                                        \
-    IQ_LAUNCH_SPAN(APP_, true, 3);                    \
+    IQ_LAUNCH_SPAN(APP_, true, 3, false);                    \
   } else if (bits == 2) {                             \
-    IQ_LAUNCH_SPAN(APP_, false, 2);                   \
+    IQ_LAUNCH_SPAN(APP_, false, 2, false);                   \
   } else if (bits == 4) {                             \
-    IQ_LAUNCH_SPAN(APP_, false, 4);                   \
+    IQ_LAUNCH_SPAN(APP_, false, 4, false);                   \
   } else {                                            \
-    IQ_LAUNCH_SPAN(APP_, false, 3);                   \
+    IQ_LAUNCH_SPAN(APP_, false, 3, false);                   \
   }
-  if (append) {
+  if (rope) {
+    IQ_LAUNCH_SPAN(false, false, 3, true);
+  } else if (append) {
     IQ_LAUNCH_SPAN_A(true)
   } else {
     IQ_LAUNCH_SPAN_A(false)

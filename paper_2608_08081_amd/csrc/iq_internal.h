@@ -183,14 +183,15 @@ struct SpanPlan {
 };
 // n_rows, n_splits as in g8_plan; false if the call does not fit the kernel.
 bool span_plan(int64_t batch, int64_t n_rows, int64_t n_splits, int64_t max_seq_len,
-               SpanPlan* plan);
+               int64_t workgroups, SpanPlan* plan);
 hipError_t launch_decode_span(const SpanPlan& plan, int64_t n_splits, const float* q,
                               uint8_t* k_codes, float* k_norms, uint8_t* v_codes, float* v_norms,
                               int32_t* seq_lens, int64_t capacity, int64_t max_seq_len,
                               const float* quats, int64_t batch, int64_t n_kv_heads,
                               int64_t group, float scale, float* out, float* partials,
                               const StepAppend* append, const PageTable* pages, int bits,
-                              hipStream_t stream, const iq_codebook_t* cb);
+                              hipStream_t stream, const iq_codebook_t* cb,
+                              const RopeKeys* rope = nullptr);
 
 // Multi-token decode on records of `bits` bits (group 8): n_tok (2..4)
 // query tokens per sequence, q / out [batch][n_tok][8 n_kv_heads][128]; the

@@ -171,3 +171,38 @@ def test_rows_of_any_length(batch, hkv, group, cap, step, shift):
     err = row_rel_err(got, ref)
     print(f"[rows] max row rel err {err.max():.3e}", flush=True)
     assert err.max() <= RTOL
+
+
+@pytest.mark.parametrize("hq,hkv,shared,kind", [(16, 16, True, "edges"), (16, 2, False, "edges"),
+                                                (8, 8, True, "one")])
+def test_positional_split(hq, hkv, shared, kind):
+    cap = 1040
+    batch = -(-16384 // (hkv * (cap // 16)))   # the shortest line that takes the kernel
+    seq = [min(n, cap) for n in _lengths(kind, batch, cap)]
+    print(f"[span rope] hq={hq} hkv={hkv} shared={shared} {kind} batch={batch}", flush=True)
+    rng = np.random.default_rng([7, hq, hkv])
+    kc, kn = _records(rng, (batch, hkv, cap), 3)
+    vc, vn = _records(rng, (batch, hkv, cap), 3)
+    kr = rng.standard_normal((batch, 1 if shared else hkv, cap, 64), dtype=np.float32).astype(
+        np.float16)
+    quats = orot.make_quaternions(79, hkv)
+    levels, _ = ocb.isoquant_codebook(128, 3)
+    q = rng.standard_normal((batch, hq, 128), dtype=np.float32)
+    qr = rng.standard_normal((batch, hq, 64), dtype=np.float32)
+    gkn, gvn, gkr = kn.copy(), vn.copy(), kr.copy()
+    for i, n in enumerate(seq):
+        gkn[i, :, n:] = np.nan
+        gvn[i, :, n:] = np.nan
+        gkr[i, :, n:] = np.nan
+    ws = api.alloc_workspace(batch, hq, hkv, cap, DEV)
+    ws.fill_(0x44)
+    out = api.iq_decode_attention_rope(_dev(q), _dev(qr), _dev(kc), _dev(gkn), _dev(gkr), _dev(vc),
+                                       _dev(gvn), _dev(np.asarray(seq, np.int32)), _dev(quats),
+                                       workspace=ws)
+    torch.cuda.synchronize()
+    ref = oatt.decode_fused_rope(q, qr, kc, kn, kr, vc, vn, seq, quats, levels)
+    got = out.cpu().numpy()
+    assert np.all(np.isfinite(got))
+    err = row_rel_err(got, ref)
+    print(f"[span rope] max row rel err {err.max():.3e}", flush=True)
+    assert err.max() <= RTOL
