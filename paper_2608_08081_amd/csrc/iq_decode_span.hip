@@ -623,19 +623,21 @@ void decode_span_kernel(
   build_pair_table(sm, cb, threadIdx.x);   // before the first span's barriers
   int b = wg / n_rows, y = wg - b * n_rows;   // the current row: sequence, row in it
   int start = 0, x = 0, x1 = 0;   // where b's rows start on the line, the run's rest x .. x1
+  int len = 0;                    // b's clamped length
   if (!by_rows) {
-    const SpanLine line =
-        span_line(seq_lens, batch, n_rows, max_seq_len, n_wg, lane, -1, &start);
-    x = wg * line.run;
-    x1 = x + line.run < line.total ? x + line.run : line.total;
+    const SpanRun run = span_run(seq_lens, batch, n_rows, max_seq_len, n_wg, lane, wg);
+    x = run.x;
+    x1 = run.x1;
     if (x >= x1) return;
-    span_find(seq_lens, batch, n_rows, max_seq_len, lane, x, &b, &start);
-    y = (x - start) / span_width(span_length(seq_lens[b], max_seq_len));
-  } else if (b >= batch) {
-    return;
+    b = run.seq;
+    start = run.start;
+    len = run.len;
+    y = (x - start) / span_width(len);
+  } else {
+    if (b >= batch) return;
+    len = span_length(seq_lens[b], max_seq_len);
   }
   for (bool first = true;;) {
-    const int len = span_length(seq_lens[b], max_seq_len);
     const int width = span_width(len);   // of each row of this sequence
     const int r = b * n_rows + y;
     // the row's part in this run: batches a0 .. a1 - 1, its new token or not
@@ -662,6 +664,7 @@ void decode_span_kernel(
       b = (r + n_wg) / n_rows;
       y = r + n_wg - b * n_rows;
       if (b >= batch) return;
+      len = span_length(seq_lens[b], max_seq_len);
     } else {
       x = e;
       if (x >= x1) return;
@@ -669,6 +672,7 @@ void decode_span_kernel(
         start += n_rows * width;
         y = 0;
         ++b;
+        len = span_length(seq_lens[b], max_seq_len);
       }
     }
   }

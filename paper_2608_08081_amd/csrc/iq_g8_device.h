@@ -658,28 +658,44 @@ __device__ __forceinline__ SpanLine span_line(const int32_t* __restrict__ lens, 
   return SpanLine{total, run < kSpanMinRun ? kSpanMinRun : run};
 }
 
-// The sequence whose rows hold batch x (< total) of the line, and where they
-// start; the same in every lane.
-__device__ __forceinline__ void span_find(const int32_t* __restrict__ lens, int batch, int n_rows,
-                                          int max_seq_len, int lane, int x, int* seq,
-                                          int* start) {
-  int base = 0;
-  *seq = batch;
+// A run's place on the line: its batches x .. x1 - 1 (none if x >= x1), and the
+// sequence whose rows hold x, where these start and its clamped length; the
+// same in every lane.  Up to 64 sequences the lengths are read once (a chain
+// of three reads, line, sequence and length, costs a short step a
+// microsecond).
+struct SpanRun {
+  int x, x1, seq, start, len;
+};
+__device__ __forceinline__ SpanRun span_run(const int32_t* __restrict__ lens, int batch, int n_rows,
+                                            int max_seq_len, int workers, int lane, int index) {
+  SpanRun r{0, 0, 0, 0, 0};
+  int base = 0, len = 0, w = 0, incl = 0;
+  auto scan = [&](int c0) {
+    len = c0 + lane < batch ? span_length(lens[c0 + lane], max_seq_len) : 0;
+    w = c0 + lane < batch ? n_rows * span_width(len) : 0;
+    incl = wave_scan(w);
+    return __builtin_amdgcn_readlane(incl, 63);
+  };
+  int total = 0;
+  for (int c0 = 0; c0 < batch; c0 += 64) total += scan(c0);
+  int run = (total + workers - 1) / workers;
+  run = run < kSpanMinRun ? kSpanMinRun : run;
+  r.x = index * run;
+  r.x1 = r.x + run < total ? r.x + run : total;
+  if (r.x >= r.x1) return r;
   for (int c0 = 0; c0 < batch; c0 += 64) {
-    const int w =
-        c0 + lane < batch ? n_rows * span_width(span_length(lens[c0 + lane], max_seq_len)) : 0;
-    const int incl = wave_scan(w);
-    const int sum = __builtin_amdgcn_readlane(incl, 63);
-    if (x < base + sum) {
+    const int sum = batch <= 64 ? total : scan(c0);
+    if (r.x < base + sum) {
       // the lanes whose inclusive sum is at most x - base come before it
-      const int i = __builtin_popcountll(__ballot(incl <= x - base));
-      *seq = c0 + i;
-      *start = base + __builtin_amdgcn_readlane(incl - w, i);
-      return;
+      const int i = __builtin_popcountll(__ballot(incl <= r.x - base));
+      r.seq = c0 + i;
+      r.start = base + __builtin_amdgcn_readlane(incl - w, i);
+      r.len = __builtin_amdgcn_readlane(len, i);
+      return r;
     }
     base += sum;
   }
-  *start = base;
+  return r;
 }
 
 // Merge of the split partials of one (sequence b, query head h): grid
