@@ -21,6 +21,13 @@
 // its chunk as two words, looks the codes up in a 64-entry LDS table of
 // level pairs and writes its 16 outputs as 32 (fp16) or 64 (fp32)
 // contiguous bytes, so the 8 lanes of a token write its row in one piece.
+//
+// The matrices are built once per workgroup, in LDS: with each lane building
+// its own four (500 of its 2100 vector instructions) 4 heads of 32768 keys and
+// values took 24.9 us as fp16 and 48.2 as fp32; now 21.5 and 46.3 (3.8 and 3.7
+// TB/s), 16 ragged sequences of up to 16000 100 -> 82.  Four passes per
+// workgroup fit four waves per SIMD (123 registers): 8 passes at three waves
+// 21.8, 86.5.
 #include <hip/hip_fp16.h>
 #include <hip/hip_runtime.h>
 
@@ -35,9 +42,10 @@ typedef float f32x2_t __attribute__((ext_vector_type(2)));
 
 constexpr int kDqWaves = 4;
 constexpr int kDqThreads = 64 * kDqWaves;
-constexpr int kDqPasses = 8;                              // passes of 8 tokens per wave
-constexpr int kDqTokens = 8 * kDqWaves * kDqPasses;       // tokens per workgroup (256)
+constexpr int kDqPasses = 4;                              // passes of 8 tokens per wave
+constexpr int kDqTokens = 8 * kDqWaves * kDqPasses;       // tokens per workgroup (128)
 constexpr float kInvSqrtDim = 0.08838834764831845f;
+constexpr int kChunkFloats = 64 + 4;                      // B_i of 4 blocks, padded
 
 // 4-point unnormalized Walsh-Hadamard butterfly
 __device__ __forceinline__ void wht4v(float& a, float& b, float& c, float& d) {
@@ -84,18 +92,22 @@ __device__ __forceinline__ void store_chunk<float>(float* dst, const float (&x)[
   for (int i = 0; i < 4; ++i) p[i] = f32x4_t{x[4 * i], x[4 * i + 1], x[4 * i + 2], x[4 * i + 3]};
 }
 
-// Workgroup: (K|V side, sequence b, KV head g, 256-token chunk).  Tokens
-// t0 .. t0 + 255 of the output come from cache positions src_offset + t;
+// Workgroup: (K|V side, sequence b, KV head g, 128-token chunk).  Tokens
+// t0 .. t0 + 127 of the output come from cache positions src_offset + t;
 // tokens at or past n_tokens, or whose cache position is at or past
 // seq_lens[b] (when given), are not written.
 template <typename TOut>
-__global__ __launch_bounds__(kDqThreads) void dequant_kernel(
+__global__ __launch_bounds__(kDqThreads) __attribute__((amdgpu_waves_per_eu(4)))
+void dequant_kernel(
     const uint8_t* __restrict__ codes0, const float* __restrict__ norms0, TOut* __restrict__ out0,
     const uint8_t* __restrict__ codes1, const float* __restrict__ norms1, TOut* __restrict__ out1,
     const float* __restrict__ quats, const int32_t* __restrict__ seq_lens, int n_heads,
     int64_t n_bh, int64_t n_tokens, int64_t chunks, int64_t capacity, int64_t src_offset,
     Codebook cb) {
   __shared__ f32x2_t pair_tab[64];   // field f -> (C[f & 7], C[f >> 3])
+  // B_i, entry (r, k) of block 4 c + bb at btab[c][bb][4 r + k]; the padding
+  // puts the 8 chunks' rows, read together, on different banks
+  __shared__ __attribute__((aligned(16))) float btab[8][kChunkFloats];
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = tid >> 6;
   const int64_t chunk = blockIdx.x % chunks;
@@ -138,24 +150,37 @@ __global__ __launch_bounds__(kDqThreads) void dequant_kernel(
     sv[p] = norms[row0 + t];
   }
 
-  // B_i = H_4 M_i^T of blocks 4c .. 4c+3 (column k of B_i = H_4 (row k of M_i))
-  float bm[4][4][4];   // [block][row r][column k]
-  const float* qh = quats + static_cast<int64_t>(g) * kQuatFloats;
-#pragma unroll
-  for (int bb = 0; bb < 4; ++bb) {
+  // B_i = H_4 M_i^T (column k of B_i = H_4 (row k of M_i)): thread (block i,
+  // k) builds column k once per workgroup
+  if (tid < 4 * kNumBlocks) {
+    const int blk = tid >> 2, k = tid & 3;
     float m[4][4];
-    so4_matrix(qh + (4 * c + bb) * 8, m);
+    so4_matrix(quats + static_cast<int64_t>(g) * kQuatFloats + 8 * blk, m);
+    float r0 = m[0][0], r1 = m[0][1], r2 = m[0][2], r3 = m[0][3];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      float r0 = m[k][0], r1 = m[k][1], r2 = m[k][2], r3 = m[k][3];
-      wht4v(r0, r1, r2, r3);
-      bm[bb][0][k] = r0;
-      bm[bb][1][k] = r1;
-      bm[bb][2][k] = r2;
-      bm[bb][3][k] = r3;
+    for (int i = 1; i < 4; ++i) {
+      r0 = k == i ? m[i][0] : r0;
+      r1 = k == i ? m[i][1] : r1;
+      r2 = k == i ? m[i][2] : r2;
+      r3 = k == i ? m[i][3] : r3;
     }
+    wht4v(r0, r1, r2, r3);
+    float* col = &btab[blk >> 2][16 * (blk & 3) + k];
+    col[0] = r0;
+    col[4] = r1;
+    col[8] = r2;
+    col[12] = r3;
   }
-  __syncthreads();   // pair table
+  __syncthreads();   // pair table, btab
+  float bm[4][4][4];   // [block][row r][column k] of blocks 4c .. 4c+3
+#pragma unroll
+  for (int bb = 0; bb < 4; ++bb)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const f32x4_t row = *reinterpret_cast<const f32x4_t*>(&btab[c][16 * bb + 4 * r]);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) bm[bb][r][k] = row[k];
+    }
 
   const float sg1 = (lane & 1) ? -1.f : 1.f, sg2 = (lane & 2) ? -1.f : 1.f;
   const float sg8 = (lane & 8) ? -1.f : 1.f;
