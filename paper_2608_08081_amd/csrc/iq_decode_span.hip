@@ -211,9 +211,8 @@ __device__ __forceinline__ void span_chunk(SpanState<kBits, kRope>& s, SpanStage
   m = cols_max(fmaxf(m, xor_lane<8>(m)));
   // ---- a new maximum or unit: what is summed so far, rescaled --------------
   if (unit != s.unit || __any(m > s.m)) {
-    // (exp2(-inf) = 0 for the first chunk; both infinite, as with scores that
-    // are not finite, gives NaN as it should)
-    const float f = __builtin_amdgcn_exp2f((s.m - m) * qdown);
+    // (nothing finite so far: 0, which leaves a NaN sum NaN)
+    const float f = s.m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((s.m - m) * qdown);
     s.l *= f;
     // the old unit over the new, exactly (0 if beyond the exponent range)
     const int de = static_cast<int>(s.unit >> 23) - static_cast<int>(unit >> 23) + 127;
@@ -231,7 +230,9 @@ __device__ __forceinline__ void span_chunk(SpanState<kBits, kRope>& s, SpanStage
   wave_lds_fence();
   // ---- weights (Table 2 B) and values (Table 2 C), as in attend_wave -------
   const uint32_t sel_hi = upper ? 0x01000808u : 0x08080504u;
-  const float mq = -m * qdown;
+  // (every score so far -inf: weights exp2(-inf) = 0; scores that are NaN,
+  // which the maximum passes over, give NaN weights and so a NaN sum)
+  const float mq = m == -INFINITY ? 0.f : -m * qdown;
 #pragma unroll
   for (int i = 0; i < NB; ++i) {
     if (!kFull && 16 * i >= nvalid) break;
@@ -719,7 +720,8 @@ __global__ __launch_bounds__(kThreads) void merge_span_kernel(
   const f32x4_t* qg =
       reinterpret_cast<const f32x4_t*>(quats + static_cast<int64_t>(g) * kQuatFloats + 8 * dq);
   const f32x4_t ql = qg[0], qr = qg[1];
-  const int len = span_length(lens[b], max_seq_len);
+  const int seq = lens[b];
+  const int len = span_length(seq, max_seq_len);
   const int nb = (len + 15) >> 4;
   int64_t slot0 = r;
   int n_spans = nb > 0 ? 1 : 0;
@@ -735,6 +737,10 @@ __global__ __launch_bounds__(kThreads) void merge_span_kernel(
   }
   const int n_iter = n_spans + (kAppend ? 1 : 0);
   const float* base = partials + hh * kPart;
+  // the new token counts if it was written (its l entry) and lies before
+  // max_seq_len; a row is empty without positions and without it
+  const bool new_near = kAppend && seq < max_seq_len;
+  bool any = n_spans > 0;
   float M = -INFINITY, L = 0.f;
   f32x4_t O = f32x4_t{0.f, 0.f, 0.f, 0.f};
   for (int s0 = sg; s0 < n_iter; s0 += kGroups * kUnroll) {
@@ -752,7 +758,12 @@ __global__ __launch_bounds__(kThreads) void merge_span_kernel(
     float Mn = M;
 #pragma unroll
     for (int u = 0; u < kUnroll; ++u) {
-      ml[u][0] = s0 + kGroups * u < n_iter ? ml[u][0] : -INFINITY;
+      const int s = s0 + kGroups * u;
+      const bool live = s < n_spans || (s < n_iter && new_near && ml[u][1] > 0.f);
+      any |= live;
+      ml[u][0] = live ? ml[u][0] : -INFINITY;
+      ml[u][1] = live ? ml[u][1] : 0.f;
+      ov[u] = live ? ov[u] : f32x4_t{0.f, 0.f, 0.f, 0.f};
       Mn = fmaxf(Mn, ml[u][0]);
     }
     const float cM = (M == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(M - Mn);
@@ -760,12 +771,10 @@ __global__ __launch_bounds__(kThreads) void merge_span_kernel(
     O *= cM;
 #pragma unroll
     for (int u = 0; u < kUnroll; ++u) {
-      // a partial without positions: selected away, not scaled
-      const bool live = ml[u][0] != -INFINITY;
-      const float c = live ? __builtin_amdgcn_exp2f(ml[u][0] - Mn) : 0.f;
-      L += live ? c * ml[u][1] : 0.f;
-#pragma unroll
-      for (int j = 0; j < 4; ++j) O[j] += live ? c * ov[u][j] : 0.f;
+      // (m = -inf: every score -inf, or NaN with l NaN, which the zero keeps)
+      const float c = ml[u][0] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(ml[u][0] - Mn);
+      L += c * ml[u][1];
+      O += c * ov[u];
     }
     M = Mn;
   }
@@ -788,9 +797,10 @@ __global__ __launch_bounds__(kThreads) void merge_span_kernel(
       o += c * red_o[j][hj][dq];
       l += c * red_l[j][hj];
     }
-    // an empty sequence gives a zero row
-    const f32x4_t res = l > 0.f ? rotate_inverse(o * (1.0f / l), ql, qr, dq)
-                                : f32x4_t{0.f, 0.f, 0.f, 0.f};
+    // an empty sequence gives a zero row, anything else o / l, also where l is
+    // NaN (without spans, this group of threads has seen the new token)
+    const f32x4_t res =
+        any ? rotate_inverse(o * (1.0f / l), ql, qr, dq) : f32x4_t{0.f, 0.f, 0.f, 0.f};
     const int64_t hq = static_cast<int64_t>(b) * n_kv_heads * group +
                        static_cast<int64_t>(g) * group + kHeads * vg + hh;
     *reinterpret_cast<f32x4_t*>(out + hq * kDim + 4 * dq) = res;
