@@ -329,7 +329,7 @@ hipError_t launch_decode(const DecodePlan& plan, const float* q, uint8_t* k_code
   SpanPlan sp;
   const int64_t n_rows = n_kv_heads * ((group + 7) / 8);
   if (plan.g8_batches > 0 && row32 && grid_ok &&
-      span_plan(batch, n_rows, plan.g8_splits, max_seq_len, 512, &sp)) {
+      span_plan(batch, n_rows, plan.g8_splits, max_seq_len, 512, 0, &sp)) {
     float* parts = reinterpret_cast<float*>(static_cast<char*>(workspace) + plan.ticket_bytes);
     return launch_decode_span(sp, plan.g8_splits, q, k_codes, k_norms, v_codes, v_norms, seq_lens,
                               capacity, max_seq_len, quats, batch, n_kv_heads, group, scale, out,

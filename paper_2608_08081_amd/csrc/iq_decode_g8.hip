@@ -138,7 +138,7 @@ void decode_g8_kernel(
     attend_split<NB, kAppend, false, kPaged, kBits, kRope>(sm, a, gsize, split, g, vg, b, bgv,
                                                           0, true);
   } else {
-    wide_items<NB, kAppend, kPaged, kBits, kRope>(sm, a, gsize, n_rows, vshift, true);
+    wide_items<NB, kAppend, kPaged, kBits, kRope>(sm, a, gsize, n_rows, vshift, true, -1);
   }
 }
 }  // namespace
@@ -210,7 +210,7 @@ hipError_t launch_decode_g8(int nb, int64_t n_splits, int64_t split_len, const f
   const int64_t span_line = span_wgs * kWaves * (rope ? 8 : 12);
   if (wide && n_splits > 1 && batch * n_rows * ((max_seq_len + 15) / 16) >= span_line) {
     SpanPlan sp;
-    if (span_plan(batch, n_rows, n_splits, max_seq_len, span_wgs, &sp) && sp.workers == span_wgs)
+    if (span_plan(batch, n_rows, n_splits, max_seq_len, span_wgs, split_len, &sp) && sp.workers == span_wgs)
       return launch_decode_span(sp, n_splits, q, k_codes, k_norms, v_codes, v_norms, seq_lens,
                                 capacity, max_seq_len, quats, batch, n_kv_heads, group, scale,
                                 out, partials, append, pages, bits, stream, cb, rope);

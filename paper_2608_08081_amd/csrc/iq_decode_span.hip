@@ -7,11 +7,12 @@
 // Work decomposition: a sequence's positions, in batches of 16, follow each
 // other row by row (row = KV head x head group of 8 query heads) and sequence
 // by sequence; two persistent workgroups per CU each take an equal run of
-// this line.  A run holds one row's part, or the end of a row, whole rows and
-// the start of another; the part of one row in one run is a span.  Rows are
-// longer by kRowBatches than their positions, for what a span costs besides
-// its batches; the workgroup whose run holds a row's start also appends the
-// row's new token (fused step).
+// this line (short lines: fixed splits, see decode_span_kernel).  A run holds
+// one row's part, or the end of a row, whole rows and the start of another;
+// the part of one row in one run is a span.  Rows are longer by kRowBatches
+// than their positions, for what a span costs besides its batches; the
+// workgroup whose run holds a row's start also appends the row's new token
+// (fused step).
 //
 // Inside a span each wave walks its own stretch of batches, kSpanBatches at a
 // time (two-phase softmax per chunk, running maximum between chunks), and the
@@ -34,7 +35,7 @@
 #include <hip/hip_runtime.h>
 #include <math.h>
 
-#include "iq_g8_device.h"
+#include "iq_g8_split.h"
 
 namespace iq {
 namespace {
@@ -596,27 +597,45 @@ __device__ __forceinline__ void attend_span(SpanSmem<kBits, kRope>& sm, const G8
 // span; a fused step's new-token partials follow the n_splits slots per row
 // that the workspace has for splits.
 //
+// Short lines (only the kernel knows the lengths, the launch a bound of them)
+// take the fixed splits of decode_g8_kernel, of split_len positions: a span's
+// start and end, and the new token beside too few batches to hide it, cost
+// more than equal runs gain.  Rows sized for 32768 positions, batch of 64 x 2
+// rows, runs / splits: steps at 100 positions 19.8 / 14.0 us, at 1000 22.5 /
+// 16.4, decode at 1000 15.2 / 13.2.  Where the line is drawn (kShortBatches),
+// mean over nine shapes of rows, pages and bits: decode of 4 batches per wave
+// 19.3 / 19.1, of 5 21.0 / 22.3; steps of 8 32.9 / 31.7, of 10 35.5 / 36.3.
+// kSplits false (rows of any length, which those cannot load): always runs.
+//
 // by_rows (workspaces of one slot per row, i.e. short sequences): the
 // workgroups take whole rows w, w + gridDim.x, ... instead, row r in slot r.
 //
 // kRope: 32 more registers of positional keys per wave, so one workgroup per
 // CU.
-template <bool kAppend, bool kPaged, int kBits, bool kRope>
+template <bool kAppend, bool kPaged, int kBits, bool kRope, bool kSplits>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kRope ? 2 : 4)))
 void decode_span_kernel(
     const float* __restrict__ q, uint8_t* __restrict__ k_codes, float* __restrict__ k_norms,
     uint8_t* __restrict__ v_codes, float* __restrict__ v_norms,
     const int32_t* __restrict__ seq_lens, const float* __restrict__ quats,
     float* __restrict__ partials, int64_t capacity, int max_seq_len, int n_kv_heads,
-    int n_splits, float qscale, CodebookB<kBits> cb, const void* __restrict__ k_new,
-    const void* __restrict__ v_new, int new_f16, int32_t* __restrict__ status, PageTable pages,
-    int group, int batch, int32_t* __restrict__ lens0, int by_rows) {
+    int n_splits, int split_len, float qscale, CodebookB<kBits> cb,
+    const void* __restrict__ k_new, const void* __restrict__ v_new, int new_f16,
+    int32_t* __restrict__ status, PageTable pages, int group, int batch,
+    int32_t* __restrict__ lens0, int by_rows_arg) {
+  const bool by_rows = !kSplits && by_rows_arg != 0;
+  // (out is written by grids of one split only)
   const G8Args<kBits> a{q,        k_codes, k_norms, v_codes,  v_norms,     seq_lens,
-                        quats,    partials, nullptr, capacity, max_seq_len, n_kv_heads,
-                        n_splits, 0,       qscale,  cb,       k_new,       v_new,
-                        new_f16,  status,  pages,   group,    batch,       lens0};
+                        quats,    partials, partials, capacity, max_seq_len, n_kv_heads,
+                        n_splits, split_len, qscale, cb,      k_new,       v_new,
+                        new_f16,  status,  pages,   group,    batch,       nullptr};
   static_assert(!kRope || (!kAppend && !kPaged && kBits == 3), "decode of 3-bit rows");
-  __shared__ __attribute__((aligned(16))) SpanSmem<kBits, kRope> sm;
+  // the LDS of a span or of a fixed split (the pair table first in both)
+  constexpr size_t kSplitLds = kSplits ? sizeof(G8Smem<kBits, kRope, false>) : 0;
+  constexpr size_t kLds =
+      sizeof(SpanSmem<kBits, kRope>) > kSplitLds ? sizeof(SpanSmem<kBits, kRope>) : kSplitLds;
+  __shared__ __attribute__((aligned(16))) char lds[kLds];
+  auto& sm = *reinterpret_cast<SpanSmem<kBits, kRope>*>(lds);
   const int vshift = group > kHeads ? 1 : 0;
   const int n_rows = n_kv_heads << vshift;
   const int wg = static_cast<int>(blockIdx.x), n_wg = static_cast<int>(gridDim.x);
@@ -625,18 +644,44 @@ void decode_span_kernel(
   int b = wg / n_rows, y = wg - b * n_rows;   // the current row: sequence, row in it
   int start = 0, x = 0, x1 = 0;   // where b's rows start on the line, the run's rest x .. x1
   int len = 0;                    // b's clamped length
+  bool splits = false;            // a short line
+  int len0 = -1;
   if (!by_rows) {
-    const SpanRun run = span_run(seq_lens, batch, n_rows, max_seq_len, n_wg, lane, wg);
+    const SpanRun run =
+        span_run<kAppend, kSplits>(seq_lens, batch, n_rows, max_seq_len, n_wg, lane, wg);
+    splits = run.splits;
+    len0 = run.first;
     x = run.x;
     x1 = run.x1;
-    if (x >= x1) return;
     b = run.seq;
     start = run.start;
     len = run.len;
-    y = (x - start) / span_width(len);
-  } else {
+  }
+  // for the merge: the clamped lengths as they are now (its workgroups of row 0
+  // advance seq_lens), the sign bit set on short lines
+  if (wg == 0) {
+    const int flag = splits ? static_cast<int>(0x80000000u) : 0;
+    if (len0 >= 0) {
+      if (threadIdx.x < batch) lens0[threadIdx.x] = len0 | flag;   // (at most 64 of wave 0)
+    } else {
+      for (int i = threadIdx.x; i < batch; i += kThreads)
+        lens0[i] = span_length(seq_lens[i], max_seq_len) | flag;
+    }
+  }
+  if constexpr (kSplits) {
+    if (__builtin_expect(splits, 1)) {
+      wide_items<kMaxBatches, kAppend, kPaged, kBits, kRope>(
+          *reinterpret_cast<G8Smem<kBits, kRope, false>*>(lds), a, group, n_rows, vshift, false,
+          len0);
+      return;
+    }
+  }
+  if (by_rows) {
     if (b >= batch) return;
     len = span_length(seq_lens[b], max_seq_len);
+  } else {
+    if (x >= x1) return;
+    y = (x - start) / span_width(len);
   }
   for (bool first = true;;) {
     const int width = span_width(len);   // of each row of this sequence
@@ -683,18 +728,21 @@ void decode_span_kernel(
 // rotation and (fused step) the advance of the lengths, as merge_g8_kernel;
 // the rows' spans are found from the line.  kHpw query heads per workgroup:
 // 8 for rows of few spans (two groups of threads share a head's spans), 1
-// for rows of many (sixteen groups).  lens: the lengths as the span kernel
-// saw them (the fused step's copy, since this launch's workgroup of row 0
-// advances seq_lens[b]).  workers: runs of the line, 0 with whole rows.
+// for rows of many (eight groups; sixteen took 0.3 us more on short lines).
+// lens0: the lengths as the span kernel saw them (see there); on short lines
+// they place the row's partials without the line.  workers: runs of the line,
+// 0 with whole rows.
 // Bound by its chain of loads (lengths, then partials): one workgroup per
 // row instead of one per query head reads the lengths an eighth as often.
+template <int kHpw>
+constexpr int merge_threads = kHpw == 1 ? 256 : 512;
 template <bool kAppend, int kHpw>
-__global__ __launch_bounds__(kThreads) void merge_span_kernel(
+__global__ __launch_bounds__(merge_threads<kHpw>) void merge_span_kernel(
     const float* __restrict__ partials, const float* __restrict__ quats, float* __restrict__ out,
     int n_kv_heads, int n_splits, int32_t* __restrict__ seq_lens,
-    const int32_t* __restrict__ lens, int64_t capacity, int group, int workers, int max_seq_len,
-    int batch) {
-  constexpr int kGroups = kHeads * 2 / kHpw;   // groups of threads per head
+    const int32_t* __restrict__ lens0, int64_t capacity, int group, int workers, int max_seq_len,
+    int batch, int split_len) {
+  constexpr int kGroups = merge_threads<kHpw> / (32 * kHpw);   // groups of threads per head
   constexpr int kUnroll = 8;
   __shared__ __attribute__((aligned(16))) f32x4_t red_o[kGroups][kHpw][32];
   __shared__ float red_m[kGroups][kHpw], red_l[kGroups][kHpw];
@@ -711,35 +759,41 @@ __global__ __launch_bounds__(kThreads) void merge_span_kernel(
   const int hh = h0 + hj;
   const int r = b * n_rows + y;
   int seq0 = 0;
-  float written = 0.f;
-  const int64_t new0 = static_cast<int64_t>(batch) * n_rows * n_splits;
-  if (kAppend && y == 0 && h0 == 0 && tid == 0) {
-    seq0 = seq_lens[b];
-    written = partials[(new0 + r) * (kHeads * kPart) + 1];
-  }
   const f32x4_t* qg =
       reinterpret_cast<const f32x4_t*>(quats + static_cast<int64_t>(g) * kQuatFloats + 8 * dq);
   const f32x4_t ql = qg[0], qr = qg[1];
-  const int seq = lens[b];
-  const int len = span_length(seq, max_seq_len);
+  const int word = lens0[b];
+  const bool splits = word < 0;
+  const int len = word & 0x7fffffff;
   const int nb = (len + 15) >> 4;
+  // the row's spans: slots slot0 .. slot0 + n_spans - 1; its new token's slot
   int64_t slot0 = r;
+  int64_t slot_new = static_cast<int64_t>(batch) * n_rows * n_splits + r;
   int n_spans = nb > 0 ? 1 : 0;
-  if (workers > 0) {
+  if (__builtin_expect(splits, 1)) {   // a short line: as the fixed splits' kernel lays them out
+    slot0 = static_cast<int64_t>(r) * (n_splits + (kAppend ? 1 : 0));
+    slot_new = slot0 + n_splits;
+    n_spans = (len + split_len - 1) / split_len;
+  } else if (workers > 0) {
     int start = 0;
     const SpanLine line =
-        span_line(lens, batch, n_rows, max_seq_len, workers, tid & 63, b, &start);
+        span_line(lens0, batch, n_rows, max_seq_len, workers, tid & 63, b, &start);
     const int width = span_width(len);
     const int at0 = start + y * width + width - nb;
     const int w0 = at0 / line.run;
     if (nb > 0) n_spans = (at0 + nb - 1) / line.run - w0 + 1;
     slot0 += w0;
   }
+  float written = 0.f;
+  if (kAppend && y == 0 && h0 == 0 && tid == 0) {
+    seq0 = seq_lens[b];
+    written = partials[slot_new * (kHeads * kPart) + 1];
+  }
   const int n_iter = n_spans + (kAppend ? 1 : 0);
   const float* base = partials + hh * kPart;
   // the new token counts if it was written (its l entry) and lies before
   // max_seq_len; a row is empty without positions and without it
-  const bool new_near = kAppend && seq < max_seq_len;
+  const bool new_near = kAppend && len < max_seq_len;
   bool any = n_spans > 0;
   float M = -INFINITY, L = 0.f;
   f32x4_t O = f32x4_t{0.f, 0.f, 0.f, 0.f};
@@ -749,7 +803,7 @@ __global__ __launch_bounds__(kThreads) void merge_span_kernel(
 #pragma unroll
     for (int u = 0; u < kUnroll; ++u) {
       const int s = s0 + kGroups * u < n_iter ? s0 + kGroups * u : s0;
-      const int64_t slot = s < n_spans ? slot0 + s : new0 + r;
+      const int64_t slot = s < n_spans ? slot0 + s : slot_new;
       const float* p = base + slot * (kHeads * kPart);
       ml[u] = *reinterpret_cast<const f32x2_t*>(p);   // (m, l)
       ov[u] = *reinterpret_cast<const f32x4_t*>(p + 2 + 4 * dq);
@@ -818,18 +872,19 @@ __global__ __launch_bounds__(kThreads) void merge_span_kernel(
 // `workgroups` of them (two per CU, one with positional keys).  false: neither
 // is possible.
 bool span_plan(int64_t batch, int64_t n_rows, int64_t n_splits, int64_t max_seq_len,
-               int64_t workgroups, SpanPlan* plan) {
+               int64_t workgroups, int64_t split_len, SpanPlan* plan) {
   const int64_t rows = batch * n_rows;
   if (rows * (n_splits + 1) > (int64_t{1} << 30)) return false;   // slots: 32-bit indices
   if (n_splits == 1) {
-    *plan = SpanPlan{static_cast<int>(rows < workgroups ? rows : workgroups), true};
+    *plan = SpanPlan{static_cast<int>(rows < workgroups ? rows : workgroups), true, 0};
     return true;
   }
   if (batch > kSpanMaxBatch ||
       rows * ((max_seq_len + 15) / 16 + kRowBatches) + workgroups > 0x3fffffff)
     return false;
   const int64_t most = rows * (n_splits - 1) + 1;
-  *plan = SpanPlan{static_cast<int>(most < workgroups ? most : workgroups), false};
+  *plan = SpanPlan{static_cast<int>(most < workgroups ? most : workgroups), false,
+                   static_cast<int>(split_len)};
   return true;
 }
 
@@ -849,29 +904,31 @@ hipError_t launch_decode_span(const SpanPlan& plan, int64_t n_splits, const floa
   const int new_f16 = append ? append->f16 : (rope ? rope->shared : 0);
   int32_t* status = append ? append->status : nullptr;
   const PageTable pt = pages ? *pages : PageTable{nullptr, 0, 4, 1};
-  int32_t* const lens0 =
-      append ? reinterpret_cast<int32_t*>(reinterpret_cast<char*>(partials) +
-                                          g8_partial_region_bytes(batch, n_rows, n_splits))
-             : nullptr;
-#define IQ_LAUNCH_SPAN(APP_, PAGED_, BITS_, ROPE_)                                              \
-  hipLaunchKernelGGL((decode_span_kernel<APP_, PAGED_, BITS_, ROPE_>), grid, block, 0, stream, q, \
-                     k_codes, k_norms, v_codes, v_norms, seq_lens, quats, partials, capacity,   \
-                     static_cast<int>(max_seq_len), static_cast<int>(n_kv_heads),               \
-                     static_cast<int>(n_splits), qscale, codebook_for<BITS_>(cb), k_new, v_new, \
-                     new_f16, status, pt, static_cast<int>(group), static_cast<int>(batch),     \
-                     lens0, plan.by_rows ? 1 : 0)
-#define IQ_LAUNCH_SPAN_A(APP_)                        \
-  if (pages) {                                        \
-    IQ_LAUNCH_SPAN(APP_, true, 3, false);                    \
-  } else if (bits == 2) {                             \
-    IQ_LAUNCH_SPAN(APP_, false, 2, false);                   \
-  } else if (bits == 4) {                             \
-    IQ_LAUNCH_SPAN(APP_, false, 4, false);                   \
-  } else {                                            \
-    IQ_LAUNCH_SPAN(APP_, false, 3, false);                   \
+  int32_t* const lens0 = reinterpret_cast<int32_t*>(
+      reinterpret_cast<char*>(partials) + g8_partial_region_bytes(batch, n_rows, n_splits));
+#define IQ_LAUNCH_SPAN(APP_, PAGED_, BITS_, ROPE_, SPLITS_)                                     \
+  hipLaunchKernelGGL((decode_span_kernel<APP_, PAGED_, BITS_, ROPE_, SPLITS_>), grid, block, 0,  \
+                     stream, q, k_codes, k_norms, v_codes, v_norms, seq_lens, quats, partials,  \
+                     capacity, static_cast<int>(max_seq_len), static_cast<int>(n_kv_heads),     \
+                     static_cast<int>(n_splits), plan.split_len, qscale,                        \
+                     codebook_for<BITS_>(cb), k_new, v_new, new_f16, status, pt,                \
+                     static_cast<int>(group), static_cast<int>(batch), lens0,                   \
+                     plan.by_rows ? 1 : 0)
+#define IQ_LAUNCH_SPAN_A(APP_)                      \
+  if (plan.split_len == 0) {                        \
+    IQ_LAUNCH_SPAN(APP_, false, 3, false, false);   \
+  } else if (pages) {                               \
+    IQ_LAUNCH_SPAN(APP_, true, 3, false, true);     \
+  } else if (bits == 2) {                           \
+    IQ_LAUNCH_SPAN(APP_, false, 2, false, true);    \
+  } else if (bits == 4) {                           \
+    IQ_LAUNCH_SPAN(APP_, false, 4, false, true);    \
+  } else {                                          \
+    IQ_LAUNCH_SPAN(APP_, false, 3, false, true);    \
   }
+  if (plan.split_len == 0 && (pages || bits != 3 || rope)) return hipErrorInvalidValue;
   if (rope) {
-    IQ_LAUNCH_SPAN(false, false, 3, true);
+    IQ_LAUNCH_SPAN(false, false, 3, true, true);
   } else if (append) {
     IQ_LAUNCH_SPAN_A(true)
   } else {
@@ -887,10 +944,11 @@ hipError_t launch_decode_span(const SpanPlan& plan, int64_t n_splits, const floa
   const dim3 mgrid(static_cast<unsigned>(few ? n_rows : n_rows * kHeads),
                    static_cast<unsigned>(batch));
 #define IQ_LAUNCH_SPAN_MERGE(APP_, HPW_)                                                        \
-  hipLaunchKernelGGL((merge_span_kernel<APP_, HPW_>), mgrid, block, 0, stream, partials, quats,  \
-                     out, static_cast<int>(n_kv_heads), static_cast<int>(n_splits), seq_lens,   \
-                     APP_ ? lens0 : seq_lens, capacity, static_cast<int>(group), runs,          \
-                     static_cast<int>(max_seq_len), static_cast<int>(batch))
+  hipLaunchKernelGGL((merge_span_kernel<APP_, HPW_>), mgrid, dim3(merge_threads<HPW_>), 0,       \
+                     stream, partials, quats, out, static_cast<int>(n_kv_heads),                \
+                     static_cast<int>(n_splits), seq_lens, lens0, capacity,                     \
+                     static_cast<int>(group), runs, static_cast<int>(max_seq_len),              \
+                     static_cast<int>(batch), plan.split_len)
   if (append && few) {
     IQ_LAUNCH_SPAN_MERGE(true, 8);
   } else if (append) {

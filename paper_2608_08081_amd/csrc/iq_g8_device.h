@@ -474,7 +474,7 @@ struct G8Args {
   int32_t* status;
   PageTable pages;
   int group, batch;
-  int32_t* lens0;   // fused steps on grids of several rounds: each sequence's length
+  int32_t* lens0;   // fused steps on grids of several rounds: each sequence's length (or null)
 };
 
 // ---- the fused step's new token -------------------------------------------
@@ -621,6 +621,15 @@ struct SpanLine {
   int run;     // batches per workgroup
 };
 
+// Short lines, which take fixed splits instead: fewer than this many batches of
+// positions for each wave (the measurements are at decode_span_kernel).
+template <bool kAppend>
+constexpr int kShortBatches = kAppend ? 9 : 5;
+template <bool kAppend>
+__device__ __forceinline__ bool short_line(int total, int batch, int n_rows, int workers) {
+  return total - batch * n_rows * kRowBatches < workers * (kWaves * kShortBatches<kAppend>);
+}
+
 __device__ __forceinline__ int span_length(int s, int max_seq_len) {
   return s < 0 ? 0 : (s > max_seq_len ? max_seq_len : s);
 }
@@ -665,10 +674,15 @@ __device__ __forceinline__ SpanLine span_line(const int32_t* __restrict__ lens, 
 // microsecond).
 struct SpanRun {
   int x, x1, seq, start, len;
+  // a short line, which takes fixed splits: then the five above are not set
+  bool splits;
+  int first;   // clamped length of sequence `lane`; -1 where there are more than 64
 };
+// kSplits: fixed splits can be taken.
+template <bool kAppend, bool kSplits>
 __device__ __forceinline__ SpanRun span_run(const int32_t* __restrict__ lens, int batch, int n_rows,
                                             int max_seq_len, int workers, int lane, int index) {
-  SpanRun r{0, 0, 0, 0, 0};
+  SpanRun r{0, 0, 0, 0, 0, false, -1};
   int base = 0, len = 0, w = 0, incl = 0;
   auto scan = [&](int c0) {
     len = c0 + lane < batch ? span_length(lens[c0 + lane], max_seq_len) : 0;
@@ -678,6 +692,11 @@ __device__ __forceinline__ SpanRun span_run(const int32_t* __restrict__ lens, in
   };
   int total = 0;
   for (int c0 = 0; c0 < batch; c0 += 64) total += scan(c0);
+  if (batch <= 64) r.first = len;
+  if (__builtin_expect(kSplits && short_line<kAppend>(total, batch, n_rows, workers), kSplits)) {
+    r.splits = true;
+    return r;
+  }
   int run = (total + workers - 1) / workers;
   run = run < kSpanMinRun ? kSpanMinRun : run;
   r.x = index * run;

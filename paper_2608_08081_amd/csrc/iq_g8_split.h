@@ -598,10 +598,11 @@ __device__ __forceinline__ void attend_split(Smem& sm, const G8Args<kBits>& a,
 
 // The work items of a persistent workgroup on a grid of several rounds: first
 // the fused step's new tokens, then the live splits (see decode_g8_kernel).
-// build_lut: the pair table is not written yet.
+// build_lut: the pair table is not written yet.  len0: the clamped length of
+// sequence `lane`, or -1 (not read yet).
 template <int NB, bool kAppend, bool kPaged, int kBits, bool kRope, class Smem>
 __device__ __forceinline__ void wide_items(Smem& sm, const G8Args<kBits>& a, int gsize, int n_rows,
-                                           int vshift, bool build_lut) {
+                                           int vshift, bool build_lut, int len0) {
   const int lane = threadIdx.x & 63;
   const int n_parts = kAppend ? a.n_splits + 1 : a.n_splits;
   const int n_app = kAppend ? a.batch * n_rows : 0;
@@ -624,28 +625,15 @@ __device__ __forceinline__ void wide_items(Smem& sm, const G8Args<kBits>& a, int
   for (int c0 = 0; c0 < a.batch; c0 += 64) {
     // the chunk's clamped lengths (lane l: sequence c0 + l) and the
     // inclusive prefix sum of their items
-    int len = 0;
-    if (c0 + lane < a.batch) {
-      const int s = a.seq_lens[c0 + lane];
-      len = s < 0 ? 0 : (s > a.max_seq_len ? a.max_seq_len : s);
-    }
+    int len = len0;
+    if (len0 < 0 || c0 > 0)
+      len = c0 + lane < a.batch ? span_length(a.seq_lens[c0 + lane], a.max_seq_len) : 0;
     // (the divisor opaque here: its reciprocal is then not held in a
     // register across the loop)
     int sl = a.split_len;
     asm volatile("" : "+s"(sl));
     const int live = c0 + lane < a.batch ? (n_parts == 1 ? 1 : (len + sl - 1) / sl) : 0;
-    int incl = live * n_rows;
-    {
-      // the lane index opaque here, so that the permute addresses are not
-      // computed once and held in registers for the whole kernel
-      int ln = lane;
-      asm volatile("" : "+v"(ln));
-#pragma unroll
-      for (int d = 1; d < 64; d <<= 1) {
-        const int t = __builtin_amdgcn_ds_bpermute(((ln - d) & 63) << 2, incl);
-        incl += ln >= d ? t : 0;
-      }
-    }
+    const int incl = wave_scan(live * n_rows);
     const int total = __builtin_amdgcn_readlane(incl, 63);
     // kept in the wave's LDS copy rather than in registers across the items
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);

@@ -98,9 +98,9 @@ bool plan_decode(int64_t batch, int64_t n_q_heads, int64_t n_kv_heads,
 // Workspace of the matrix-core path after the reserved bytes: the partials
 // of every (sequence, row, split or new token) in this many bytes (rows =
 // KV heads x head groups), then one int32 per sequence: in fused steps on
-// grids of several rounds, the length each sequence had when the step
-// began, recorded by its append workgroup for the merge (whose workgroup of
-// head 0 advances seq_lens while the others still need the old length).
+// grids of several rounds and in the span kernel, the length each sequence
+// had when the step began, recorded for the merge (whose workgroup of head 0
+// advances seq_lens while the others still need the old length).
 inline size_t g8_partial_region_bytes(int64_t batch, int64_t rows, int64_t n_splits) {
   const size_t b = static_cast<size_t>(batch) * rows * (n_splits + 1) * 8 * (2 + kDim) * 4;
   return (b + 255) / 256 * 256;
@@ -177,13 +177,16 @@ hipError_t launch_decode_g8(int nb, int64_t n_splits, int64_t split_len, const f
 // The span kernel (iq_decode_span.hip): launch_decode_g8's work for grids of
 // many work items, and for rows that are not whole batches of 16 positions.
 // workers: its workgroups; by_rows: they take whole rows instead of runs.
+// split_len: positions of the fixed splits that short lines take, 0 for none.
 struct SpanPlan {
   int workers;
   bool by_rows;
+  int split_len;
 };
-// n_rows, n_splits as in g8_plan; false if the call does not fit the kernel.
+// n_rows, n_splits, split_len as in g8_plan (split_len 0: rows that fixed
+// splits cannot load); false if the call does not fit the kernel.
 bool span_plan(int64_t batch, int64_t n_rows, int64_t n_splits, int64_t max_seq_len,
-               int64_t workgroups, SpanPlan* plan);
+               int64_t workgroups, int64_t split_len, SpanPlan* plan);
 hipError_t launch_decode_span(const SpanPlan& plan, int64_t n_splits, const float* q,
                               uint8_t* k_codes, float* k_norms, uint8_t* v_codes, float* v_norms,
                               int32_t* seq_lens, int64_t capacity, int64_t max_seq_len,

@@ -4,6 +4,9 @@ oracle: lengths around every chunk, wave and batch edge, empty sequences, runs
 that hold several rows and rows that cross runs, 2-, 3- and 4-bit records,
 pages, head groups other than 8, and a single long sequence among empty ones."""
 
+import os
+import re
+
 import numpy as np
 import pytest
 import torch
@@ -13,6 +16,7 @@ from oracle import codebook as ocb
 from oracle import compress as ocz
 from oracle import rotation as orot
 from paper_2608_08081_amd import api
+from paper_2608_08081_amd import build as B
 from tests.parity import row_rel_err
 
 pytestmark = pytest.mark.gpu
@@ -44,19 +48,9 @@ def _lengths(kind, batch, cap):
     return [cap - 1 if i == batch // 2 else 0 for i in range(batch)]   # "one"
 
 
-@pytest.mark.parametrize("bits,group,kind,page,step", [
-    (3, 8, "edges", 0, True), (3, 8, "edges", 0, False), (3, 8, "one", 0, True),
-    (3, 8, "one", 0, False), (2, 8, "edges", 0, True), (4, 8, "edges", 0, True),
-    (3, 4, "edges", 16, True), (3, 16, "edges", 64, False), (3, 5, "full", 0, True),
-])
-def test_span_against_oracle(bits, group, kind, page, step):
-    hkv, cap = 2, 2112
-    rows = hkv * (2 if group > 8 else 1)
-    batch = -(-49152 // (rows * (cap // 16)))   # the shortest line that takes the kernel
-    seq = _lengths(kind, batch, cap)
-    print(f"[span] bits={bits} group={group} {kind} page={page} step={step} batch={batch}",
-          flush=True)
-    rng = np.random.default_rng([5, bits, group, page])
+def _check(rng, seq, bits, group, page, step, hkv, cap):
+    """One decode or fused step of sequences of these lengths against the oracle."""
+    batch = len(seq)
     kc, kn = _records(rng, (batch, hkv, cap), bits)
     vc, vn = _records(rng, (batch, hkv, cap), bits)
     quats = orot.make_quaternions(77, hkv)
@@ -113,6 +107,76 @@ def test_span_against_oracle(bits, group, kind, page, step):
     err = row_rel_err(got, ref)
     print(f"[span] max row rel err {err.max():.3e}", flush=True)
     assert err.max() <= RTOL
+
+
+@pytest.mark.parametrize("bits,group,kind,page,step", [
+    (3, 8, "edges", 0, True), (3, 8, "edges", 0, False), (3, 8, "one", 0, True),
+    (3, 8, "one", 0, False), (2, 8, "edges", 0, True), (4, 8, "edges", 0, True),
+    (3, 4, "edges", 16, True), (3, 16, "edges", 64, False), (3, 5, "full", 0, True),
+])
+def test_span_against_oracle(bits, group, kind, page, step):
+    hkv, cap = 2, 2112
+    rows = hkv * (2 if group > 8 else 1)
+    batch = -(-49152 // (rows * (cap // 16)))   # the shortest line that takes the kernel
+    seq = _lengths(kind, batch, cap)
+    print(f"[span] bits={bits} group={group} {kind} page={page} step={step} batch={batch}",
+          flush=True)
+    _check(np.random.default_rng([5, bits, group, page]), seq, bits, group, page, step, hkv, cap)
+
+
+def _short_batches(step):
+    src = open(os.path.join(B.CSRC, "iq_g8_device.h")).read()
+    both = re.search(r"kShortBatches = kAppend \? (\d+) : (\d+);", src)
+    return int(both.group(1 if step else 2))
+
+
+def _line_of(rng, batch, batches, cap, step):
+    """Lengths of `batch` sequences with `batches` 16-position batches in all, empty ones and every
+    remainder among them."""
+    nb = rng.multinomial(batches, rng.dirichlet(np.full(batch, 4.0)))
+    nb[1] += nb[0]
+    nb[0] = 0
+    top = (cap - 16) // 16
+    while nb.max() > top:   # move what does not fit to the shortest
+        i, j = int(nb.argmax()), 2 + int(nb[2:].argmin())
+        nb[j] += nb[i] - top
+        nb[i] = top
+    n = 16 * nb - rng.integers(0, 16, size=batch)
+    assert nb.sum() == batches
+    return [int(max(x, 0)) for x in n]
+
+
+@pytest.mark.parametrize("bits,group,page,step,over", [
+    (3, 8, 0, True, 0), (3, 8, 0, True, 1), (3, 8, 0, False, 0), (3, 8, 0, False, 1),
+    (3, 8, 16, True, 0), (3, 8, 16, True, 1), (3, 16, 64, False, 0), (3, 16, 64, False, 1),
+    (2, 8, 0, True, 0), (2, 5, 0, False, 1), (4, 8, 0, True, 1), (4, 8, 0, False, 0),
+    (3, 8, 0, True, -20000), (3, 3, 32, True, -20000), (3, 8, 0, False, -12000),
+])
+@pytest.mark.parametrize("batch", [40, 150])
+def test_lines_around_the_shortest_of_runs(bits, group, page, step, over, batch):
+    """Lines of the length from which the kernel takes equal runs (over 0), the longest that takes
+    fixed splits (1 batch less; over 1) and much shorter ones, in rows that could hold more."""
+    hkv = 2
+    rows = batch * hkv * (2 if group > 8 else 1)
+    # the shortest line that takes the kernel
+    cap = -(-(-(-49152 // rows) * 16 + 64) // 64) * 64
+    least = 512 * 8 * _short_batches(step) // (rows // batch)
+    batches = least - (over if over >= 0 else -over // (rows // batch))
+    rng = np.random.default_rng([9, bits, group, page, step, abs(over), batch])
+    seq = _line_of(rng, batch, batches, cap, step)
+    _check(rng, seq, bits, group, page, step, hkv, cap)
+
+
+@pytest.mark.parametrize("bits,group,page,step", [(3, 8, 0, True), (3, 8, 0, False),
+                                                  (2, 8, 0, True), (4, 16, 0, True),
+                                                  (3, 4, 16, True), (3, 8, 64, False)])
+def test_runs_with_edges(bits, group, page, step):
+    """Lengths around every edge among rows long enough for equal runs."""
+    hkv, cap = 2, 2112
+    batch = -(-49152 // (hkv * (2 if group > 8 else 1) * (cap // 16)))
+    seq = [EDGES[(i // 4) % len(EDGES)] if i % 4 == 0 else cap - 1 - (37 * i) % 300
+           for i in range(batch)]
+    _check(np.random.default_rng([10, bits, group, page]), seq, bits, group, page, step, hkv, cap)
 
 
 @pytest.mark.parametrize("batch,hkv,group,cap,step,shift", [
@@ -174,11 +238,16 @@ def test_rows_of_any_length(batch, hkv, group, cap, step, shift):
 
 
 @pytest.mark.parametrize("hq,hkv,shared,kind", [(16, 16, True, "edges"), (16, 2, False, "edges"),
-                                                (8, 8, True, "one")])
+                                                (8, 8, True, "one"), (16, 16, True, "runs"),
+                                                (16, 2, False, "runs"), (8, 8, True, "splits")])
 def test_positional_split(hq, hkv, shared, kind):
     cap = 1040
     batch = -(-16384 // (hkv * (cap // 16)))   # the shortest line that takes the kernel
-    seq = [min(n, cap) for n in _lengths(kind, batch, cap)]
+    if kind in ("runs", "splits"):   # the shortest line of equal runs, or the longest of splits
+        seq = _line_of(np.random.default_rng(11), batch, 256 * 8 * _short_batches(False) // hkv -
+                       (kind == "splits"), cap, False)
+    else:
+        seq = [min(n, cap) for n in _lengths(kind, batch, cap)]
     print(f"[span rope] hq={hq} hkv={hkv} shared={shared} {kind} batch={batch}", flush=True)
     rng = np.random.default_rng([7, hq, hkv])
     kc, kn = _records(rng, (batch, hkv, cap), 3)
