@@ -206,7 +206,7 @@ __device__ __forceinline__ void compress_half(const T* __restrict__ src, const f
   }
   double ss = (a0 + a1) + (a2 + a3);
   // the two halves' sums (the same sum in both lanes: addition commutes)
-  ss += xor_lane64_f64<1>(ss);
+  ss += xor_lane64_f64<1>(ss, 0);
   const double s = sqrt(ss);
   const bool finite = ss < static_cast<double>(INFINITY);
 

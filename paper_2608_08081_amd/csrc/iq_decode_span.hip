@@ -48,7 +48,7 @@ static_assert(16 * kSpanBatches == 64, "a chunk's scales are one per lane");
 constexpr int kCompressBatches = 2;
 // buffer descriptors: raw, unformatted dwords
 constexpr int kBufferFlags = 0x00020000;
-// smallest value-scale unit (see span_scale): keeps 2^14 / unit finite
+// smallest value-scale unit (see span_chunk): keeps 2^14 / unit finite
 constexpr uint32_t kMinScaleBits = (127u - 100u) << 23;
 
 struct SpanStage {
@@ -163,7 +163,7 @@ __device__ __forceinline__ void span_chunk(SpanState<kBits, kRope>& s, SpanStage
   constexpr int NB = kSpanBatches;
   const bool upper = col >= 8;
   const int rs = upper ? 2 : 0;
-  // ---- the chunk's scales to LDS, the values' in units of 2^unit ----------
+  // ---- the chunk's scales to LDS, the values' in units of unit / 2^14 -----
   uint32_t unit;
   {
     const float v = kFull || lane < nvalid ? s.vs : 0.f;
@@ -439,6 +439,10 @@ __device__ __forceinline__ void attend_span(SpanSmem<kBits, kRope>& sm, const G8
   const uint32_t vsh = static_cast<uint32_t>(8 * (kBits * col - uoff));
   const int voff = 4 * grp * kRB + uoff;
   auto load_v = [&](int at) {
+    // (opaque here: the records' offsets then stay in the instructions instead
+    // of three registers set before the loop)
+    int vo = voff;
+    asm volatile("" : "+v"(vo));
 #pragma unroll
     for (int i = 0; i < NB; ++i) {
       const int t = at + 16 * i < last16 ? at + 16 * i : last16;
@@ -447,7 +451,7 @@ __device__ __forceinline__ void attend_span(SpanSmem<kBits, kRope>& sm, const G8
           const_cast<uint8_t*>(vc + (dlt[i] + t) * kRB), 0, n * kRB, kBufferFlags);
 #pragma unroll
       for (int r = 0; r < 4; ++r)
-        s.vw[i][r] = __builtin_amdgcn_raw_buffer_load_b32(rsrc, voff + r * kRB, 0, 0);
+        s.vw[i][r] = __builtin_amdgcn_raw_buffer_load_b32(rsrc, vo + r * kRB, 0, 0);
     }
     __builtin_amdgcn_sched_barrier(0);
   };
@@ -458,10 +462,13 @@ __device__ __forceinline__ void attend_span(SpanSmem<kBits, kRope>& sm, const G8
 
   // ---- while the loads fly: the rotated query as operands in LDS ----------
   if (tid < kRotThreads) {
-    const f32x4_t y = rotate_forward(qv, ql, qr, qblk, kInvSqrtDim * a.qscale);
+    // (opaque, like tid: the product is not held in a register between spans)
+    float qscale = a.qscale;
+    asm volatile("" : "+s"(qscale));
+    const f32x4_t y = rotate_forward(qv, ql, qr, qblk, kInvSqrtDim * qscale);
     // the positional part, scaled like the scores, shares the head's operand
     // scale
-    const f32x4_t yr = qrv * a.qscale;
+    const f32x4_t yr = qrv * qscale;
     float amx = fmaxf(fmaxf(fabsf(y[0]), fabsf(y[1])), fmaxf(fabsf(y[2]), fabsf(y[3])));
     if constexpr (kRope)
       amx = fmaxf(amx,

@@ -113,13 +113,15 @@ __device__ __forceinline__ float xor_lane(float v) {
   }
 }
 
-// Value of lane (lane ^ m) for any m < 64 (xor 32 through the permute unit).
+// Value of lane (lane ^ m) for any m < 64 (xor 32 through the permute unit;
+// lane: the lane's index).
 template <int kM>
-__device__ __forceinline__ float xor_lane64(float v) {
+__device__ __forceinline__ float xor_lane64(float v, int lane) {
   if constexpr (kM < 32) {
     return xor_lane<kM>(v);
   } else {
-    return __shfl_xor(v, kM);
+    return __builtin_bit_cast(float, __builtin_amdgcn_ds_bpermute(
+                                         (lane ^ kM) << 2, __builtin_bit_cast(int, v)));
   }
 }
 
@@ -129,16 +131,16 @@ __device__ __forceinline__ float xor_lane64(float v) {
 // the serial chain is short.
 
 template <int kM>
-__device__ __forceinline__ double xor_lane64_f64(double v) {
+__device__ __forceinline__ double xor_lane64_f64(double v, int lane) {
   const float2 p = __builtin_bit_cast(float2, v);
-  return __builtin_bit_cast(double, float2{xor_lane64<kM>(p.x), xor_lane64<kM>(p.y)});
+  return __builtin_bit_cast(double, float2{xor_lane64<kM>(p.x, lane), xor_lane64<kM>(p.y, lane)});
 }
 
 // One butterfly stage of the cross-lane Walsh-Hadamard transform (partner
 // lane l ^ kM), on the lane's two partial sums.
 template <int kM>
 __device__ __forceinline__ void wave_butterfly(float& a, float& c, int lane) {
-  const float pa = xor_lane64<kM>(a), pc = xor_lane64<kM>(c);
+  const float pa = xor_lane64<kM>(a, lane), pc = xor_lane64<kM>(c, lane);
   const bool upper = (lane & kM) != 0;
   a = upper ? pa - a : a + pa;
   c = upper ? pc - c : c + pc;
@@ -178,12 +180,12 @@ __device__ __forceinline__ WaveCode compress_vector_wave(float x0, float x1, con
   constexpr int kThr = (1 << kBits) - 1;
   double ss = static_cast<double>(x0) * static_cast<double>(x0) +
               static_cast<double>(x1) * static_cast<double>(x1);
-  ss += xor_lane64_f64<1>(ss);
-  ss += xor_lane64_f64<2>(ss);
-  ss += xor_lane64_f64<4>(ss);
-  ss += xor_lane64_f64<8>(ss);
-  ss += xor_lane64_f64<16>(ss);
-  ss += xor_lane64_f64<32>(ss);
+  ss += xor_lane64_f64<1>(ss, lane);
+  ss += xor_lane64_f64<2>(ss, lane);
+  ss += xor_lane64_f64<4>(ss, lane);
+  ss += xor_lane64_f64<8>(ss, lane);
+  ss += xor_lane64_f64<16>(ss, lane);
+  ss += xor_lane64_f64<32>(ss, lane);
   const double s = sqrt(ss);
   float a = x0 + x1, c = x0 - x1;   // stage 1 (dims 2l, 2l+1)
   wave_butterfly<1>(a, c, lane);
@@ -233,7 +235,8 @@ __device__ __forceinline__ WaveCode compress_vector_wave(float x0, float x1, con
 #pragma unroll
   for (int k = 0; k < kFields; ++k) {
     const int f = f_lo + k;
-    const uint32_t v = static_cast<uint32_t>(__shfl(static_cast<int>(fld), f & 63));
+    const uint32_t v = static_cast<uint32_t>(
+        __builtin_amdgcn_ds_bpermute((f & 63) << 2, static_cast<int>(fld)));
     const int sh = kFw * f - 32 * w;
     if (f < 64 && sh < 32) word |= sh >= 0 ? (v << sh) : (v >> (-sh));
   }

@@ -104,3 +104,29 @@ def test_multi_token_kernel_budget(tmp_path):
             assert lds <= LDS_PER_CU
         else:
             assert lds + pad <= LDS_PER_CU
+
+
+def test_span_kernel_budget(tmp_path):
+    """Span kernel instances (decode and fused step x (3-bit rows of any length; 3-bit rows and
+    pages, 2- and 4-bit rows with fixed splits for short lines), and decode with positional keys):
+    no scratch, two workgroups per CU (one with positional keys); its merge: no scratch."""
+    ks = _kernels(_device_asm("iq_decode_span.hip", tmp_path))
+    span = {n: v for n, v in ks.items() if "decode_span_kernel" in n}
+    merge = {n: v for n, v in ks.items() if "merge_span_kernel" in n}
+    assert len(span) == 11 and len(merge) == 4, sorted(ks)
+    for name, (vg, lds, priv) in span.items():
+        rope = re.search(r"decode_span_kernelILb\dELb\dELi\dELb(\d)E", name).group(1) == "1"
+        assert priv == 0, f"{name}: scratch {priv}"
+        assert vg <= (256 if rope else 128), f"{name}: {vg} VGPRs"
+        assert 2 * lds <= LDS_PER_CU, f"{name}: {lds} B LDS"
+    for name, (vg, lds, priv) in merge.items():
+        assert priv == 0 and vg <= 128, f"{name}: {vg} VGPRs, scratch {priv}"
+
+
+def test_dequant_kernel_budget(tmp_path):
+    """Materialization: no scratch, four waves per SIMD."""
+    dq = {n: v for n, v in _kernels(_device_asm("iq_dequant.hip", tmp_path)).items()
+          if "dequant_kernel" in n}
+    assert len(dq) == 2
+    for name, (vg, lds, priv) in dq.items():
+        assert priv == 0 and vg <= 128, f"{name}: {vg} VGPRs, scratch {priv}"
