@@ -248,8 +248,20 @@ iq_status iq_decode_workspace_init(void* workspace, size_t workspace_bytes,
  * capacity * 48 < 2^31 run on the matrix cores (query heads in groups of 8
  * per KV head; batch and n_kv_heads * ceil(group / 8) <= 65535; batch <= 512
  * where the capacity is not a multiple of 16 or a scale array is not 16-byte
- * aligned and rows are split), other caches on a vector-unit path with the
- * same results to rounding.
+ * aligned and rows are split), other caches on a vector-unit path.
+ * The matrix cores take the rotated query and the products of softmax weight
+ * and value scale as pairs of fp16 values (hi + lo), accumulated in fp32: the
+ * query's entries to 2^-23 and to 2^-39 of the largest, the products to 2^-21
+ * (2^-23 on rows of any length) and to 2^-38 of the largest value scale among
+ * the positions that a wave attends together (a few batches of 16, or its
+ * stretch of a long row), so that a value scale 2^15 times the others costs
+ * these bits even where its weight is negligible.  The vector units compute in
+ * fp32.
+ * Results of the two differ by rounding (both about 3e-7 to 6e-7 off the
+ * exact result in the 2-norm).
+ * A non-finite query, attended scale or new token makes the rows that attend
+ * it non-finite on the vector units, on rows of any length and on long lines
+ * of work; other calls may give zeros there instead.
  */
 iq_status iq_decode_attention(const float* q,
                               const uint8_t* k_codes, const float* k_norms,

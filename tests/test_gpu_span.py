@@ -275,3 +275,58 @@ def test_positional_split(hq, hkv, shared, kind):
     err = row_rel_err(got, ref)
     print(f"[span rope] max row rel err {err.max():.3e}", flush=True)
     assert err.max() <= RTOL
+
+
+def _decode(q, kc, kn, vc, vn, seq, quats):
+    out = api.iq_decode_attention(_dev(q), _dev(kc), _dev(kn), _dev(vc), _dev(vn),
+                                  _dev(np.asarray(seq, np.int32)), _dev(quats))
+    torch.cuda.synchronize()
+    return out.cpu().numpy().astype(np.float64)
+
+
+def test_weights_are_not_cut():
+    """One attended position (weight 1) in each of 512 sequences: over random value scales, the
+    output over the scale is the output of scale 1.  Pairs of fp16 values to nearest are off by at
+    most 2^-23, 2^-24 rms and 0 in the mean, so the mean of 512 is within 4 * 2^-24 / sqrt(512) =
+    1.1e-8 (the roundings of the outputs themselves average out over 512 x 128); pairs that are cut
+    are off by -7e-8 in the mean."""
+    batch, group, cap = 512, 8, 3
+    rng = np.random.default_rng(12)
+    kc = rng.integers(0, 256, size=(batch, 1, cap, 48), dtype=np.uint8)
+    vc = rng.integers(0, 256, size=(batch, 1, cap, 48), dtype=np.uint8)
+    kn = np.ones((batch, 1, cap), np.float32)
+    vn = rng.uniform(1.0, 2.0, size=(batch, 1, cap)).astype(np.float32)
+    quats = orot.make_quaternions(82, 1)
+    q = rng.standard_normal((batch, group, 128), dtype=np.float32)
+    one = _decode(q, kc, kn, vc, kn, [1] * batch, quats)
+    got = _decode(q, kc, kn, vc, vn, [1] * batch, quats) / vn[:, :, :1].astype(np.float64)
+    shift = (got * one).sum() / (one * one).sum() - 1.0
+    print(f"[weights] shift {shift:.2e}", flush=True)
+    assert abs(shift) <= 2e-8
+
+
+@pytest.mark.parametrize("ratio", [1e3, 1e5])
+def test_outlier_among_the_value_scales(ratio):
+    """A value scale far above the others at a position of negligible weight: weights times scales
+    are kept to 2^-39 of the largest scale of a wave's stretch (2^-25 in units of which the largest
+    is 2^14 to 2^15), so that n positions of levels below 0.19 and a rotation (norm 1) are off by
+    at most n 2^-39 0.19 sqrt(128) of that scale, beside the usual relative error."""
+    cap, n, group = 1031, 1030, 8
+    rng = np.random.default_rng(13)
+    kc = rng.integers(0, 256, size=(1, 1, cap, 48), dtype=np.uint8)
+    vc = rng.integers(0, 256, size=(1, 1, cap, 48), dtype=np.uint8)
+    kn = np.full((1, 1, cap), 14.0, np.float32)
+    vn = np.full((1, 1, cap), 14.0, np.float32)
+    quats = orot.make_quaternions(83, 1)
+    levels, _ = ocb.isoquant_codebook(128, 3)
+    rot = orot.rotation_matrices(quats)[0]
+    # queries against position 5's key: its score is the lowest by far
+    key = levels[ocz.unpack(kc[0, 0, 5][None], 128, 3)[0]] @ rot
+    q = (rng.standard_normal((1, group, 128)) - 40.0 * key / np.linalg.norm(key)).astype(np.float32)
+    vn[0, 0, 5] *= ratio
+    got = _decode(q, kc, kn, vc, vn, [n], quats)
+    ref = oatt.decode_fused(q, kc, kn, vc, vn, [n], quats, levels)
+    bound = RTOL * np.abs(ref).max(-1) + n * 2.0 ** -39 * 0.19 * 128 ** 0.5 * 14.0 * ratio
+    err = np.abs(got - ref).max(-1)
+    print(f"[outlier {ratio:g}] {err.max():.3e} bound {bound.min():.3e} out {np.abs(ref).max():.3e}")
+    assert np.all(err <= bound)
