@@ -650,7 +650,7 @@ def alloc_paged_cache(n_pages, n_kv_heads, page_size, device):
     return c
 
 
-def _paged_pools(pool, block_tables, dev):
+def _paged_pools(pool, block_tables, dev, batch=0):
     if pool["k_codes"].dim() != 4:
         raise ValueError("k_codes must be [n_pages][n_kv_heads][page_size][48]")
     n_pages, hkv, page, _ = pool["k_codes"].shape
@@ -663,6 +663,8 @@ def _paged_pools(pool, block_tables, dev):
                  dev)
     if block_tables.dim() != 2:
         raise ValueError("block_tables must be [batch][max_pages]")
+    if block_tables.shape[0] < batch:
+        raise ValueError(f"block_tables has {block_tables.shape[0]} rows for {batch} sequences")
     _require(block_tables, "block_tables", torch.int32, tuple(block_tables.shape), dev)
     return n_pages, hkv, page, block_tables.shape[1]
 
@@ -705,7 +707,7 @@ def iq_decode_attention_paged(q, pool, block_tables, seq_lens, quats, out=None,
     b, hq, _ = q.shape
     dev = q.device
     _require(q, "q", torch.float32, (b, hq, HEAD_DIM), dev)
-    n_pages, hkv, page, max_pages = _paged_pools(pool, block_tables, dev)
+    n_pages, hkv, page, max_pages = _paged_pools(pool, block_tables, dev, b)
     _require(seq_lens, "seq_lens", torch.int32, (b,), dev)
     _require(quats, "quats", torch.float32, (hkv, 32, 2, 4), dev)
     if max_seq_len is None:
@@ -739,7 +741,7 @@ def iq_decode_step_paged(q, k_new, v_new, pool, block_tables, seq_lens, quats, o
     b, hq, _ = q.shape
     dev = q.device
     _require(q, "q", torch.float32, (b, hq, HEAD_DIM), dev)
-    n_pages, hkv, page, max_pages = _paged_pools(pool, block_tables, dev)
+    n_pages, hkv, page, max_pages = _paged_pools(pool, block_tables, dev, b)
     _require(k_new, "k_new", k_new.dtype, (b, hkv, HEAD_DIM), dev)
     _require(v_new, "v_new", k_new.dtype, (b, hkv, HEAD_DIM), dev)
     _require(seq_lens, "seq_lens", torch.int32, (b,), dev)
@@ -772,7 +774,7 @@ def iq_decode_attention_multi_paged(q, pool, block_tables, seq_lens, quats, out=
     b, t, hq, _ = q.shape
     dev = q.device
     _require(q, "q", torch.float32, (b, t, hq, HEAD_DIM), dev)
-    n_pages, hkv, page, max_pages = _paged_pools(pool, block_tables, dev)
+    n_pages, hkv, page, max_pages = _paged_pools(pool, block_tables, dev, b)
     _require(seq_lens, "seq_lens", torch.int32, (b,), dev)
     _require(quats, "quats", torch.float32, (hkv, 32, 2, 4), dev)
     if max_seq_len is None:

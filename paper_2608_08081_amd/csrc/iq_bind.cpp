@@ -281,8 +281,10 @@ struct Pools {
     kn = a.tensor(i + 1, kF32, {pages, h, page});
     vc = a.tensor(i + 2, kU8, {pages, h, page, IQ_RECORD_BYTES});
     vn = a.tensor(i + 3, kF32, {pages, h, page});
+    // (a row for every sequence; more than the batch has are not read)
     const auto ts = a.sizes(i + 4, 2);
     most = ts[1];
+    if (ts[0] < b) a.ok = false;
     tab = a.tensor(i + 4, kI32, {ts[0], most});
     lens = a.tensor(i + 5, kI32, {b});
     quats = a.tensor(i + 6, kF32, {h, 32, 2, 4});

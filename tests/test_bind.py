@@ -96,3 +96,47 @@ def test_calls_go_to_the_current_stream():
         graph.replay()
         torch.cuda.synchronize()
         assert torch.equal(out2, want)
+
+
+class _General:   # a native module that never calls
+    def __getattr__(self, name):
+        return lambda *a: None
+
+
+def _paged_case(b=3, hkv=2, page=16, per=4, dev="cuda:0"):
+    c, quats, q, k, out, ws = _case(b, hkv, 8, page * per)
+    pool = api.alloc_paged_cache(b * per, hkv, page, dev)
+    for name, x in pool.items():   # page i of sequence s: s * per + i
+        y = c[name].view(b, hkv, per, page, *c[name].shape[3:]).transpose(1, 2)
+        x.copy_(y.reshape(x.shape))
+    tables = torch.arange(b * per, dtype=torch.int32, device=dev).view(b, per)
+    return c, pool, tables, quats, q, k, out, ws
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("general", [False, True])
+def test_page_tables_need_a_row_per_sequence(general, monkeypatch):
+    """Fewer rows than sequences are refused before anything runs; more are allowed."""
+    c, pool, tables, quats, q, k, out, ws = _paged_case()
+    if general:
+        monkeypatch.setattr(_lib, "native", lambda: _General())
+    lens = c["seq_lens"]
+    want = api.iq_decode_attention(q, c["k_codes"], c["k_norms"], c["v_codes"], c["v_norms"], lens,
+                                   quats).clone()
+    more = torch.cat((tables, torch.full((2, tables.shape[1]), 1 << 30, dtype=torch.int32,
+                                         device=tables.device)))
+    for t in (tables, more):
+        assert torch.equal(want, api.iq_decode_attention_paged(q, pool, t, lens, quats, out=out,
+                                                               workspace=ws))
+    before = {n: x.clone() for n, x in pool.items()}
+    qs = torch.stack((q, q), 1)
+    for t in (tables[:2], tables[:0]):
+        for call in (lambda: api.iq_decode_attention_paged(q, pool, t, lens, quats, out=out,
+                                                           workspace=ws),
+                     lambda: api.iq_decode_step_paged(q, k, k, pool, t, lens, quats, out=out,
+                                                      workspace=ws),
+                     lambda: api.iq_decode_attention_multi_paged(qs, pool, t, lens, quats)):
+            with pytest.raises(ValueError, match="rows for 3 sequences"):
+                call()
+    assert lens.tolist() == [40] * 3
+    assert all(torch.equal(x, before[n]) for n, x in pool.items())
