@@ -19,6 +19,7 @@
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/autograd/python_variable.h>
 
+#include <exception>
 #include <initializer_list>
 
 #include "isoquant.h"
@@ -134,27 +135,48 @@ struct Args {
   }
 };
 
+// The interpreter lock, given back for a scope; taken again also when an
+// exception leaves it.
+struct Unlocked {
+  PyThreadState* const state = PyEval_SaveThread();
+  Unlocked() = default;
+  Unlocked(const Unlocked&) = delete;
+  ~Unlocked() { PyEval_RestoreThread(state); }
+};
+
 // Runs one entry point: `body` fills its arguments and returns a callable that
-// makes the call (used only when every argument is fit).
+// makes the call (used only when every argument is fit).  An exception before
+// the call leaves it to the general path; one out of the call is an error: it
+// may have launched, so it is not made again.
 template <class Body>
 PyObject* run(PyObject* const* v, Py_ssize_t n, Py_ssize_t want, Body body) {
+  bool called = false;
   try {
     Args a(v, n, want);
     if (!a.ok) Py_RETURN_NONE;
-    int status = -1;
+    int status = 0;
     body(a, [&](auto call) {
       if (!a.ok) return;
       const hipStream_t stream = a.stream();
-      Py_BEGIN_ALLOW_THREADS;
+      called = true;
+      const Unlocked u;
       status = call(stream);
-      Py_END_ALLOW_THREADS;
     });
-    if (status < 0) Py_RETURN_NONE;
+    if (!called) Py_RETURN_NONE;
     return PyLong_FromLong(status);
-  } catch (...) {   // e.g. a tensor without storage: the general path reports it
-    PyErr_Clear();
-    Py_RETURN_NONE;
+  } catch (const std::exception& e) {   // e.g. a tensor without storage
+    if (called) {
+      PyErr_SetString(PyExc_RuntimeError, e.what());
+      return nullptr;
+    }
+  } catch (...) {
+    if (called) {
+      PyErr_SetString(PyExc_RuntimeError, "unknown exception");
+      return nullptr;
+    }
   }
+  PyErr_Clear();
+  Py_RETURN_NONE;
 }
 
 template <class T>

@@ -1,6 +1,8 @@
 """The native argument checks of the binding: what they leave to the general
 path (CPU), and that both paths give the same results and errors (GPU)."""
 
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -140,3 +142,28 @@ def test_page_tables_need_a_row_per_sequence(general, monkeypatch):
                 call()
     assert lens.tolist() == [40] * 3
     assert all(torch.equal(x, before[n]) for n, x in pool.items())
+
+
+@pytest.mark.gpu
+def test_an_exception_out_of_the_call_is_an_error():
+    """Bound to a function that throws: the call raises, with the interpreter lock held, and is
+    not made a second time by the general path."""
+    c, quats, q, k, out, ws = _case()
+    throw = ctypes.cast(getattr(ctypes.CDLL("libstdc++.so.6"), "_ZSt17__throw_bad_allocv"),
+                        ctypes.c_void_p).value
+    nat = _lib.native()
+    out.fill_(7.0)
+    try:
+        nat.bind(*[throw] * len(_lib._BOUND))
+        with pytest.raises(RuntimeError, match="bad_alloc"):
+            api.iq_decode_step(q, k, k, c["k_codes"], c["k_norms"], c["v_codes"], c["v_norms"],
+                               c["seq_lens"], quats, out=out, workspace=ws)
+    finally:
+        nat.bind(*(ctypes.cast(getattr(_lib.lib(), n), ctypes.c_void_p).value
+                   for n in _lib._BOUND))
+    torch.cuda.synchronize()
+    assert torch.all(out == 7.0) and c["seq_lens"].tolist() == [40, 40]
+    api.iq_decode_step(q, k, k, c["k_codes"], c["k_norms"], c["v_codes"], c["v_norms"],
+                       c["seq_lens"], quats, out=out, workspace=ws)
+    assert c["seq_lens"].tolist() == [41, 41]
+
