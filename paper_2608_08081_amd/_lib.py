@@ -1,7 +1,8 @@
 """ctypes loader for libisoquant.so (the C ABI in include/isoquant.h).
 
 Loading never falls back to anything: if the shared library has not been
-built, every entry point raises.
+built, every entry point raises.  (The native argument checks of the binding
+are an addition to it: see native().)
 """
 
 from __future__ import annotations
@@ -9,6 +10,7 @@ from __future__ import annotations
 import ctypes
 import os
 import re
+import warnings
 
 _PKG = os.path.dirname(os.path.abspath(__file__))
 # IQ_LIB_PATH selects another build of the same library (e.g. the
@@ -159,17 +161,29 @@ _BOUND = ("iq_compress_kv", "iq_compress_kv_bits", "iq_decode_attention",
 _native = None
 
 
+class _NoNative:
+    """Stands in for _bind where it cannot be loaded: makes no call, so that every
+    call takes the general path."""
+
+    def __getattr__(self, name):
+        return lambda *args: None
+
+
 def native():
     """The native argument checks (module _bind), tied to lib()'s functions.
-    Raises if it is not built."""
+    Where it does not load (it is built for one torch and one Python; the
+    library is not), a warning, once, and the general path for every call."""
     global _native
     if _native is None:
         handle = lib()
         try:
             from . import _bind
         except ImportError as e:
-            raise RuntimeError("paper_2608_08081_amd/_bind.so is missing or does not load: build "
-                               "it with __graft_entry__.build()") from e
+            warnings.warn(f"paper_2608_08081_amd/_bind.so does not load ({e}): calls take 5 to 11 "
+                          "us longer; build it with __graft_entry__.build()", RuntimeWarning,
+                          stacklevel=2)
+            _native = _NoNative()
+            return _native
         _bind.bind(*(ctypes.cast(getattr(handle, n), ctypes.c_void_p).value for n in _BOUND))
         _native = _bind
     return _native

@@ -167,3 +167,17 @@ def test_an_exception_out_of_the_call_is_an_error():
                        c["seq_lens"], quats, out=out, workspace=ws)
     assert c["seq_lens"].tolist() == [41, 41]
 
+
+
+def test_without_the_native_module_every_call_takes_the_general_path(monkeypatch):
+    import sys
+
+    import paper_2608_08081_amd as package
+    monkeypatch.setattr(_lib, "_native", None)
+    monkeypatch.delattr(package, "_bind", raising=False)
+    monkeypatch.setitem(sys.modules, package.__name__ + "._bind", None)
+    with pytest.warns(RuntimeWarning, match="_bind.so does not load"):
+        nat = _lib.native()
+    assert nat.decode(*[None] * 12) is None and _lib.native() is nat
+    with pytest.raises(ValueError):   # reported by the general path
+        api.iq_decode_attention(torch.zeros(1, 8, 64), *[torch.zeros(1)] * 6)
