@@ -214,13 +214,14 @@ __device__ __forceinline__ void compress_half(const T* __restrict__ src, const f
   // zero vector keeps the plain thresholds, so its all-zero y maps to the
   // first non-negative level.
   double sc = ss > 0.0 ? s * 11.313708498984760390 : 1.0;   // sqrt(128)
-  // fp32 inputs near the top of the range: scaled down by an exact power of
-  // two, so that no sum overflows (|y| and every partial sum are below 12 s)
-  // and y - T is a number
+  // fp32 inputs whose sums could overflow (|y|, T and every partial sum are at
+  // most sqrt(128) s): scaled down by an exact power of two, so that y - T is a
+  // number.  Not below that: entries far smaller than s would leave the range,
+  // and they decide a code where the large ones cancel
   if constexpr (sizeof(T) == 4) {
-    const bool large = ss >= 0x1p200;
+    const bool large = ss >= 0x1p248;
     if (__any(large)) {
-      const float f = large ? 0x1p-64f : 1.0f;
+      const float f = large ? 0x1p-16f : 1.0f;
       sc *= static_cast<double>(f);
 #pragma unroll
       for (int i = 0; i < kHalfDim; ++i) x[i] *= f;

@@ -65,3 +65,25 @@ def test_codes_at_the_edges(bits, dtype, identity):
                 f"signs b={bits}")
     far = ~near
     assert np.all((g == codes)[far] | (np.abs(np.abs(y[far])[:, None] - np.abs(thr)).min(-1) < 1e-6))
+
+
+@pytest.mark.parametrize("bits", [2, 3, 4])
+@pytest.mark.parametrize("exponent", [60, 100, 123])
+def test_small_entries_decide_where_large_ones_cancel(bits, exponent):
+    """x0 = x1 = 2^e and x2 = -1e-30, identity blocks: coordinates whose signs of x0 and x1 differ
+    are +-x2 exactly, so their codes are the levels beside zero on x2's side."""
+    x = np.zeros((1, 1, 128, 128), np.float32)
+    x[..., 0] = x[..., 1] = 2.0 ** exponent
+    x[..., 2] = -1e-30
+    quats = np.zeros((1, 32, 2, 4), np.float32)
+    quats[..., 0] = 1.0
+    c = api.alloc_cache(1, 1, 128, DEV, bits=bits)
+    xd = torch.from_numpy(x).to(DEV)
+    api.iq_compress_kv_bits(xd, xd, torch.from_numpy(quats).to(DEV), c["k_codes"], c["k_norms"],
+                            c["v_codes"], c["v_norms"], bits=bits)
+    torch.cuda.synchronize()
+    had = orot.hadamard(128)
+    cancel = had[:, 0] * had[:, 1] < 0
+    want = 2 ** (bits - 1) - (had[cancel, 2] > 0)
+    got = ocz.unpack(c["k_codes"].cpu().numpy(), 128, bits)[0, 0]
+    assert np.array_equal(got[:, cancel], np.broadcast_to(want, got[:, cancel].shape))
