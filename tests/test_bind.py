@@ -181,3 +181,114 @@ def test_without_the_native_module_every_call_takes_the_general_path(monkeypatch
     assert nat.decode(*[None] * 12) is None and _lib.native() is nat
     with pytest.raises(ValueError):   # reported by the general path
         api.iq_decode_attention(torch.zeros(1, 8, 64), *[torch.zeros(1)] * 6)
+
+
+def _calls():
+    """Every entry point of the native module: name -> (function, its arguments)."""
+    c, pool, tables, quats, q, k, out, ws = _paged_case()
+    b, hkv, cap = c["k_norms"].shape
+    rows = dict(k_codes=c["k_codes"], k_norms=c["k_norms"], v_codes=c["v_codes"],
+                v_norms=c["v_norms"])
+    at = dict(seq_lens=c["seq_lens"], quats=quats)
+    dev = q.device
+    g = torch.Generator(device=dev).manual_seed(4)
+    q2 = torch.randn((b, 2, 16, 128), generator=g, device=dev)
+    k2 = torch.randn((b, 2, hkv, 128), generator=g, device=dev)
+    ws2 = torch.empty(api.iq_decode_multi_workspace_bytes(b, 2, 16, hkv, cap), dtype=torch.uint8,
+                      device=dev)
+    x = torch.randn((b, hkv, 9, 128), generator=g, device=dev)
+    io = dict(out=out, workspace=ws)
+    io2 = dict(out=torch.empty_like(q2), workspace=ws2)
+    flag = torch.zeros(1, dtype=torch.int32, device=dev)
+    kv = torch.empty((b, hkv, cap, 128), dtype=torch.float16, device=dev)
+    n = {}
+    n["compress"] = (api.iq_compress_kv, dict(k=x, v=x, quats=quats, **rows, dst_offset=48))
+    n["decode"] = (api.iq_decode_attention, dict(q=q, **rows, **at, **io))
+    n["step"] = (api.iq_decode_step, dict(q=q, k_new=k, v_new=k, **rows, **at, **io, status=flag))
+    n["paged"] = (api.iq_decode_attention_paged, dict(q=q, pool=pool, block_tables=tables, **at,
+                                                      **io))
+    n["step_paged"] = (api.iq_decode_step_paged, dict(q=q, k_new=k, v_new=k, pool=pool,
+                                                      block_tables=tables, **at, **io,
+                                                      status=flag))
+    n["multi"] = (api.iq_decode_attention_multi, dict(q=q2, **rows, **at, **io2))
+    n["step_multi"] = (api.iq_decode_step_multi, dict(q=q2, k_new=k2, v_new=k2, **rows, **at,
+                                                      **io2, status=flag))
+    n["rope"] = (api.iq_decode_attention_rope, dict(
+        q=q, q_rope=torch.randn((b, 16, 64), generator=g, device=dev), **rows,
+        k_rope=torch.randn((b, 1, cap, 64), generator=g, device=dev).half(), **at, **io))
+    n["dequantize"] = (api.iq_dequantize_kv, dict(**rows, quats=quats, k_out=kv,
+                                                  v_out=torch.empty_like(kv)))
+    return n, (c["k_codes"], c["k_norms"], c["v_codes"], c["v_norms"], c["seq_lens"], flag,
+               *pool.values())
+
+
+ENTRIES = ("compress", "decode", "step", "paged", "step_paged", "multi", "step_multi", "rope",
+           "dequantize")
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("name", ENTRIES)
+def test_every_entry_point_agrees_with_the_general_path(name, monkeypatch):
+    got = []
+    for general in (False, True):
+        calls, state = _calls()
+        if general:
+            monkeypatch.setattr(_lib, "native", lambda: _General())
+        else:   # the native path takes it
+            nat, taken = _lib.native(), []
+
+            class Watch:
+                def __getattr__(self, fn):
+                    return lambda *a: taken.append(getattr(nat, fn)(*a)) or taken[-1]
+
+            monkeypatch.setattr(_lib, "native", lambda: Watch())
+        f, kw = calls[name]
+        r = f(**kw)
+        if not general:
+            assert taken == [0]
+        outs = [] if r is None else ([r] if torch.is_tensor(r) else list(r))
+        got.append([x.clone() for x in (*outs, *state)])
+    assert len(got[0]) == len(got[1])
+    for x, y in zip(*got):
+        assert torch.equal(x, y)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("name", ENTRIES)
+def test_wrong_tensors_of_every_entry_point(name, monkeypatch):
+    """Each tensor in turn of another type, shape, layout or device: both paths raise the same
+    error, and nothing is written."""
+    wrong = {"type": lambda t: t.double(), "shape": lambda t: t.unsqueeze(0),
+             "layout": lambda t: torch.stack((t, t), -1)[..., 0], "device": lambda t: t.cpu(),
+             "kind": lambda t: t.cpu().numpy()}
+    calls, state = _calls()
+    f, kw = calls[name]
+    before = [x.clone() for x in state]
+    native = _lib.native
+    seen = 0
+    for arg, t in kw.items():
+        for key in (t if isinstance(t, dict) else [None]):
+            x = t[key] if key else t
+            if not torch.is_tensor(x):
+                continue
+            for how, change in wrong.items():
+                if arg == "workspace" and how in ("shape", "kind"):
+                    continue   # any shape of bytes will do
+                if name in ("paged", "step_paged", "rope") and arg == "workspace":
+                    continue   # (these take it as it is)
+                if how == "layout" and x.numel() == 1:
+                    continue   # one value is contiguous whatever its stride
+                bad = dict(kw)
+                bad[arg] = {**t, key: change(x)} if key else change(x)
+                errors = []
+                for general in (False, True):
+                    monkeypatch.setattr(_lib, "native", (lambda: _General()) if general else native)
+                    with pytest.raises((TypeError, ValueError, AttributeError,
+                                        _lib.IsoQuantError)) as e:
+                        f(**bad)
+                    errors.append((e.type, str(e.value)))
+                assert errors[0] == errors[1], (arg, how)
+                seen += 1
+    assert seen > 20
+    torch.cuda.synchronize()
+    assert all(torch.equal(x, y) for x, y in zip(before, state))

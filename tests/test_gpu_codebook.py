@@ -1,6 +1,6 @@
 """GPU parity with fitted codebooks (Sec. 3.2 Step 3 on calibration data):
 iq_fit_codebook's levels drive compression (iq_compress_kv_cb), decode
-(iq_decode_attention_cb, both the matrix-core and the generic path), the
+(iq_decode_attention_cb, groups of 8 and of 4 query heads), the
 fused step (iq_decode_step_cb) and materialization (iq_dequantize_kv_cb),
 each against the oracle run with the oracle's own fitted codebook (equal to
 the library's bit for bit, pinned on the CPU)."""
@@ -41,7 +41,7 @@ def _fitted(w, quats, bits, seed):
 
 @pytest.mark.parametrize("bits,hq,hkv,seq", [
     (3, 16, 2, [1000, 17, 0]),        # group 8: matrix-core path
-    (3, 8, 2, [700, 333]),            # group 4: generic path
+    (3, 8, 2, [700, 333]),            # group 4
     (2, 16, 2, [512, 31]),
     (4, 32, 4, [1500]),
 ])

@@ -48,8 +48,10 @@ def _lengths(kind, batch, cap):
     return [cap - 1 if i == batch // 2 else 0 for i in range(batch)]   # "one"
 
 
-def _check(rng, seq, bits, group, page, step, hkv, cap):
-    """One decode or fused step of sequences of these lengths against the oracle."""
+def _check(rng, seq, bits, group, page, step, hkv, cap, most=None, unmapped=()):
+    """One decode or fused step of sequences of these lengths against the oracle: outputs, lengths,
+    the capacity flag, and every byte of the cache.  Positions from `most` on are not attended; the
+    page of the new token is not mapped for the sequences `unmapped`."""
     batch = len(seq)
     kc, kn = _records(rng, (batch, hkv, cap), bits)
     vc, vn = _records(rng, (batch, hkv, cap), bits)
@@ -58,50 +60,63 @@ def _check(rng, seq, bits, group, page, step, hkv, cap):
     q = rng.standard_normal((batch, hkv * group, 128), dtype=np.float32)
     k_new = rng.standard_normal((batch, hkv, 128), dtype=np.float32)
     v_new = rng.standard_normal((batch, hkv, 128), dtype=np.float32)
-    gk, gkn, gv, gvn = kc.copy(), kn.copy(), vc.copy(), vn.copy()
+    room = [step and n < cap and i not in unmapped for i, n in enumerate(seq)]
     for i, n in enumerate(seq):   # a read of a position that is not attended shows up
-        gkn[i, :, n:] = np.nan
-        gvn[i, :, n:] = np.nan
+        end = n if most is None else min(n, most)
+        kn[i, :, end:] = np.nan
+        vn[i, :, end:] = np.nan
     lens = _dev(np.asarray(seq, np.int32))
-    ws = api.alloc_workspace(batch, hkv * group, hkv, cap, DEV)
+    flag = torch.zeros(1, dtype=torch.int32, device=DEV)
+    ws = api.alloc_workspace(batch, hkv * group, hkv, most or cap, DEV)
     ws.fill_(0x44)
+    host = {"k_codes": kc, "k_norms": kn, "v_codes": vc, "v_norms": vn}
     if page:
         per = cap // page
+        assert per * page == cap
         table = rng.permutation(batch * per).astype(np.int32).reshape(batch, per)
-        cache = {}
-        for nm, x in (("k_codes", gk), ("k_norms", gkn), ("v_codes", gv), ("v_norms", gvn)):
-            pool = np.empty((batch * per, hkv, page, *x.shape[3:]), x.dtype)
-            pool[table.reshape(-1)] = np.moveaxis(
-                x[:, :, :per * page].reshape(batch, hkv, per, page, *x.shape[3:]), 2, 1).reshape(
-                    batch * per, hkv, page, *x.shape[3:])
-            cache[nm] = _dev(pool)
-        tab = _dev(table)
-        assert max(seq) < per * page
+
+        def pool_of(x):
+            y = np.empty((batch * per, hkv, page, *x.shape[3:]), x.dtype)
+            y[table.reshape(-1)] = np.moveaxis(x.reshape(batch, hkv, per, page, *x.shape[3:]), 2,
+                                               1).reshape(y.shape)
+            return y
+
+        cache = {nm: _dev(pool_of(x)) for nm, x in host.items()}
+        mapped = table.copy()
+        for i in unmapped:
+            assert seq[i] % page == 0
+            mapped[i, seq[i] // page:] = (-1, 1 << 30)[i % 2]
+        tab = _dev(mapped)
     else:
-        cache = {"k_codes": _dev(gk), "k_norms": _dev(gkn), "v_codes": _dev(gv),
-                 "v_norms": _dev(gvn)}
-    args = (cache["k_codes"], cache["k_norms"], cache["v_codes"], cache["v_norms"], lens,
-            _dev(quats))
+        cache = {nm: _dev(x) for nm, x in host.items()}
+    args = (*cache.values(), lens, _dev(quats))
+    kw = dict(workspace=ws, max_seq_len=most)
     if step and page:
         out = api.iq_decode_step_paged(_dev(q), _dev(k_new), _dev(v_new), cache, tab, lens,
-                                       _dev(quats), workspace=ws)
+                                       _dev(quats), status=flag, **kw)
     elif step:
-        out = api.iq_decode_step_bits(_dev(q), _dev(k_new), _dev(v_new), *args, workspace=ws,
-                                      bits=bits)
+        out = api.iq_decode_step_bits(_dev(q), _dev(k_new), _dev(v_new), *args, status=flag,
+                                      bits=bits, **kw)
     elif page:
-        out = api.iq_decode_attention_paged(_dev(q), cache, tab, lens, _dev(quats), workspace=ws)
+        out = api.iq_decode_attention_paged(_dev(q), cache, tab, lens, _dev(quats), **kw)
     else:
-        out = api.iq_decode_attention_bits(_dev(q), *args, workspace=ws, bits=bits)
+        out = api.iq_decode_attention_bits(_dev(q), *args, bits=bits, **kw)
     torch.cuda.synchronize()
+    assert lens.cpu().tolist() == [n + r for n, r in zip(seq, room)]
+    assert int(flag) == (5 if step and not all(room) else 0)   # IQ_ERR_CAPACITY
     if step:
-        assert lens.cpu().tolist() == [n + 1 for n in seq]
         rots = orot.rotation_matrices(quats)
         pk, nk, *_ = ocz.compress_kv(k_new[:, :, None], rots, thr)
         pv, nv, *_ = ocz.compress_kv(v_new[:, :, None], rots, thr)
         for i, n in enumerate(seq):
-            kc[i, :, n], kn[i, :, n] = pk[i, :, 0], nk[i, :, 0]
-            vc[i, :, n], vn[i, :, n] = pv[i, :, 0], nv[i, :, 0]
-    ref = oatt.decode_fused(q, kc, kn, vc, vn, [n + step for n in seq], quats, levels)
+            if room[i]:
+                kc[i, :, n], kn[i, :, n] = pk[i, :, 0], nk[i, :, 0]
+                vc[i, :, n], vn[i, :, n] = pv[i, :, 0], nv[i, :, 0]
+    for nm, x in host.items():   # the new records, and nothing else
+        got = cache[nm].cpu().numpy()
+        assert np.array_equal(got, pool_of(x) if page else x, equal_nan=nm.endswith("norms")), nm
+    end = [min(n + r, most or cap) for n, r in zip(seq, room)]
+    ref = oatt.decode_fused(q, kc, np.nan_to_num(kn), vc, np.nan_to_num(vn), end, quats, levels)
     got = out.cpu().numpy()
     assert np.all(np.isfinite(got))
     err = row_rel_err(got, ref)
@@ -115,7 +130,7 @@ def _check(rng, seq, bits, group, page, step, hkv, cap):
     (3, 4, "edges", 16, True), (3, 16, "edges", 64, False), (3, 5, "full", 0, True),
 ])
 def test_span_against_oracle(bits, group, kind, page, step):
-    hkv, cap = 2, 2112
+    hkv, cap = 2, 2112   # (33 pages of 64)
     rows = hkv * (2 if group > 8 else 1)
     batch = -(-49152 // (rows * (cap // 16)))   # the shortest line that takes the kernel
     seq = _lengths(kind, batch, cap)
@@ -229,6 +244,11 @@ def test_rows_of_any_length(batch, hkv, group, cap, step, shift):
             vc[i, :, n], vn[i, :, n] = pv[i, :, 0], nv[i, :, 0]
         assert np.array_equal(args[0].cpu().numpy(), kc)   # nothing else was written
         assert np.array_equal(args[2].cpu().numpy(), vc)
+        for got, want in ((args[1], kn), (args[3], vn)):
+            x = want.copy()
+            for i, n in enumerate(seq):
+                x[i, :, n + 1:] = np.nan
+            assert np.array_equal(got.cpu().numpy(), x, equal_nan=True)
     ref = oatt.decode_fused(q, kc, kn, vc, vn, [n + step for n in seq], quats, levels)
     got = out.cpu().numpy()
     assert np.all(np.isfinite(got))
@@ -275,6 +295,77 @@ def test_positional_split(hq, hkv, shared, kind):
     err = row_rel_err(got, ref)
     print(f"[span rope] max row rel err {err.max():.3e}", flush=True)
     assert err.max() <= RTOL
+
+
+@pytest.mark.parametrize("page", [0, 16])
+@pytest.mark.parametrize("mode", ["runs", "splits"])
+def test_sequences_without_room(page, mode):
+    """Among others: sequences at capacity (paged: also with an unmapped page for the new token)
+    are attended as they are, keep their length and raise the flag."""
+    hkv, cap = 2, 2112
+    batch = -(-49152 // (hkv * (cap // 16)))
+    rng = np.random.default_rng([14, page])
+    seq = [cap - 1 - (37 * i) % 300 if mode == "runs" else (61 * i) % 700 for i in range(batch)]
+    for i in (0, 5, batch - 1):
+        seq[i] = cap
+    unmapped = ()
+    if page:
+        unmapped = (2, 3, 40)
+        for i in unmapped:
+            seq[i] = seq[i] // page * page
+    _check(rng, seq, 3, 8, page, True, hkv, cap, unmapped=unmapped)
+
+
+@pytest.mark.parametrize("page,step,most", [(0, True, 1500), (0, False, 1500), (64, True, 1472)])
+def test_lengths_beyond_max_seq_len(page, step, most):
+    """Lengths at and past max_seq_len: the positions before it, the new token only if it lies
+    before it too (it is appended all the same)."""
+    hkv, cap = 2, 2112
+    batch = -(-49152 // (hkv * (most // 16)))
+    rng = np.random.default_rng([15, page, step])
+    seq = [(most - 1, most, most + 1, cap - 1, 17, most - 16)[i] if i < 6 else
+           int(rng.integers(most - 200, cap - 1)) for i in range(batch)]
+    _check(rng, seq, 3, 8, page, step, hkv, cap, most=most)
+
+
+def test_page_entries_of_long_runs():
+    """Runs of more than 512 batches, whose waves read their page entries in pieces of 64 batches:
+    the same bits as on rows."""
+    batch, hkv, group, page, n = 2, 8, 2, 32, 270000
+    cap = -(-n // page) * page
+    g = torch.Generator(device=DEV).manual_seed(16)
+    per = cap // page
+    order = torch.randperm(batch * per, generator=g, device=DEV).view(batch, per)
+    rows, pool = [], {}
+    for side in ("k", "v"):
+        codes = torch.randint(0, 256, (batch, hkv, cap, 48), generator=g, device=DEV,
+                              dtype=torch.uint8)
+        norms = 14.0 * torch.exp(0.35 * torch.randn((batch, hkv, cap), generator=g, device=DEV))
+        for name, x in (("codes", codes), ("norms", norms)):
+            y = x.view(batch, hkv, per, page, *x.shape[3:]).transpose(1, 2).flatten(0, 1)
+            pool[f"{side}_{name}"] = torch.empty_like(y)
+            pool[f"{side}_{name}"][order.view(-1)] = y
+            rows.append(x)
+    q = torch.randn((batch, hkv * group, 128), generator=g, device=DEV)
+    lens = torch.tensor([n, n - 12345], dtype=torch.int32, device=DEV)
+    quats = api.iq_make_rotation(17, hkv).to(DEV)
+    want = api.iq_decode_attention(q, *rows, lens, quats)
+    got = api.iq_decode_attention_paged(q, pool, order.int(), lens, quats)
+    torch.cuda.synchronize()
+    assert torch.isfinite(want).all() and want.abs().min(-1).values.max() > 0
+    assert torch.equal(got, want)
+
+
+@pytest.mark.parametrize("step", [False, True])
+def test_more_sequences_than_the_line_holds(step):
+    """513 sequences of split rows of odd capacity: the vector-unit path."""
+    hkv, cap, batch = 1, 1001, 513
+    rng = np.random.default_rng([18, step])
+    seq = [(cap - 1, 0, 1, 512, 513)[i] if i < 5 else int(rng.integers(0, cap)) for i in
+           range(batch)]
+    if step:
+        seq[6] = cap   # no room
+    _check(rng, seq, 3, 8, 0, step, hkv, cap)
 
 
 def _decode(q, kc, kn, vc, vn, seq, quats):

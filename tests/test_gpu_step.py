@@ -79,13 +79,13 @@ def _check_new_records(cache, ora, seq0, cap, label):
     (32, 4, [2999, 1500], 3008),
     (8, 1, [4095], 4096),
     (8, 1, [4096], 4112),
-    (8, 1, [4096], 4100),       # capacity not a multiple of 16: generic path
+    (8, 1, [4096], 4100),       # rows of any length: span kernel
     (8, 1, [30000], 32768),     # one KV head: more than 64 partials per row
     # a grid of several rounds (64 sequences x 2 KV heads x 4 partials): the
     # instance that reads the length before its loads and skips empty splits
     (16, 2, [0, 1, 15, 16, 17, 31, 32, 33, 63, 64, 65, 127, 128, 129, 223, 224, 225, 447,
              448, 449, 500, 600, 638, 639] + [(97 * i + 13) % 639 for i in range(40)], 640),
-    # other group sizes: append kernel, then the generic decode
+    # other group sizes (the last in rows of any length)
     (16, 4, [0, 700, 1023], 1024),
     (6, 2, [300], 301),
 ])
@@ -185,7 +185,7 @@ def test_step_beyond_max_seq_len():
 @pytest.mark.parametrize("hq,hkv,seq0,cap", [
     (32, 4, [8191], 8208),
     (16, 2, [17, 0, 1000], 1024),
-    (32, 4, [8191], 8200),      # capacity not a multiple of 16: generic path
+    (32, 4, [8191], 8200),      # rows of any length: span kernel
 ])
 def test_step_equals_append_then_decode(hq, hkv, seq0, cap):
     """Fused step and the two separate calls on identical caches: identical

@@ -2,7 +2,7 @@
 static device scratch) against iq_decode_step with a caller workspace, on
 twin caches: identical outputs, records and lengths.  Two calls in a row on
 one GPU, the second on a smaller input (the scratch keeps the first call's
-contents), then a group size that takes the generic path, a grid of several
+contents), then another group size, a grid of several
 rounds, and a shape whose workspace exceeds the scratch (rejected on the
 host)."""
 
@@ -55,7 +55,7 @@ def test_noalloc_step_equals_workspace_step_twice():
     # second call, smaller input: the scratch holds the first call's partials
     w2 = synth.Workload(8, "noalloc_small", 3, 16, 2, 1024, "f16", rotation_seed=1008)
     _compare(w2, [1000, 37, 1024], 1024, 4, "small step, one sequence at capacity")
-    # group 4 (generic path: append kernel, split kernel, combine kernel)
+    # group 4
     w3 = synth.Workload(9, "noalloc_g4", 2, 16, 4, 700, "f16", rotation_seed=1009)
     _compare(w3, [699, 5], 704, 5, "group 4")
 
