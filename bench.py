@@ -107,8 +107,8 @@ def parse():
 
 # sources of the decode step's kernels and their launch path: the counter
 # figures in profiles/ hold only while these are unchanged
-DECODE_SOURCES = ("iq_api.cpp", "iq_decode.hip", "iq_decode_g8.hip", "iq_g8_device.h",
-                  "iq_device.h", "iq_internal.h")
+DECODE_SOURCES = ("iq_api.cpp", "iq_decode.hip", "iq_decode_g8.hip", "iq_decode_span.hip",
+                  "iq_g8_split.h", "iq_g8_device.h", "iq_device.h", "iq_internal.h")
 
 
 def source_digest() -> str:
@@ -592,7 +592,7 @@ def run_varlen(args, torch, api, synth, dev):
         f"query heads, {w.n_kv_heads} KV heads, head_dim 128, contexts uniform in "
         f"[{w.varlen[0]}, {w.varlen[1]}] (seeded); {nl} distinct layer caches cycled",
         w, layers, nl, us_per_step, decode_us, wall, args,
-        "iq_decode_step per call = decode_g8_kernel<NB, append> + merge_g8_kernel<append>; "
+        "iq_decode_step per call = decode_span_kernel<append> + merge_span_kernel<append>; "
         f"algorithmic bytes = {BYTES_PER_TOKEN_HEAD} B x attended positions x KV heads + the "
         "appended tokens' inputs and records",
         {"lengths_min": int(lengths.min()), "lengths_max": int(lengths.max())})
@@ -620,8 +620,8 @@ def run_paged(args, torch, api, synth, dev):
         f"{w.n_kv_heads} KV heads, head_dim 128, contexts uniform in [{w.varlen[0]}, "
         f"{w.varlen[1]}] (seeded); {nl} distinct layer pools cycled",
         w, layers, nl, us_per_step, decode_us, wall, args,
-        "iq_decode_step_paged per call = decode_g8_kernel<NB, append, wide, paged> + "
-        f"merge_g8_kernel; algorithmic bytes = {BYTES_PER_TOKEN_HEAD} B x attended positions x "
+        "iq_decode_step_paged per call = decode_span_kernel<append, paged> + "
+        f"merge_span_kernel; algorithmic bytes = {BYTES_PER_TOKEN_HEAD} B x attended positions x "
         "KV heads + the appended tokens' inputs and records",
         {"page_size": page, "lengths_min": int(lengths.min()),
          "lengths_max": int(lengths.max())})

@@ -320,10 +320,11 @@ hipError_t launch_decode(const DecodePlan& plan, const float* q, uint8_t* k_code
   }
   // Rows that are not whole batches of 16 positions, or scales that are not
   // 16-byte aligned (a cache sized prompt + output): the span kernel, whose
-  // loads end with the row and take scales one by one.  One sequence of 8700
-  // positions in rows of 9192, 4 KV heads: 105 us per step on the vector-unit
-  // kernels below, 24 here; 16 ragged sequences of up to 6000: 243 and 24.
-  // Those kernels keep what the span kernel cannot address: rows over 2 GiB,
+  // loads end with the row and take scales one by one, at every length: the
+  // vector-unit kernels below are slower throughout (steps of 4 rows of 15
+  // positions 27 us against 13, of 1001 47 against 17; one sequence of 8700 in
+  // rows of 9192, 4 KV heads, 105 and 17; 16 ragged sequences of up to 6000 243
+  // and 22).  Those keep what the span kernel cannot address: rows over 2 GiB,
   // more than 65535 sequences or rows, and (several splits per row) more than
   // kSpanMaxBatch sequences.
   SpanPlan sp;

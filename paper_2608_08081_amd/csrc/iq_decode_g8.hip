@@ -200,12 +200,15 @@ hipError_t launch_decode_g8(int nb, int64_t n_splits, int64_t split_len, const f
   // attention, and splits past a length take no workgroup.
   constexpr int64_t kCus = 256;
   const bool wide = n_parts * n_rows * batch > kCus;
-  // The span kernel for long lines of work: where the longest rows give each
-  // wave of two workgroups per CU at least 12 batches (3 of its chunks).  With
-  // fewer a wave's last, partial chunk weighs too much: 8 batches per wave
-  // (batch 8 x 4 rows, 16K positions, 4 bits) 30.5 us in fixed splits, 30.2 to
-  // 32.4 in spans; 13 (ragged, at most 25: paged 24 x 8 rows) 40.2 and 39.7; 34
-  // (batch 64 x 2 rows, ragged, at most 64) 84.5 and 68.4.
+  // The span kernel where lines can be long: the longest rows give each wave of
+  // two workgroups per CU at least 12 batches (3 of its chunks), with positional
+  // keys each wave of one workgroup per CU at least 8.  (Only the kernel knows
+  // the lengths: short lines of such calls take the fixed splits there.)  Full
+  // rows just above the line, fixed splits / span kernel: steps of 16 x 8 rows
+  // of 6400 (12.5 batches per wave) 40.8 / 37.2 us, 32 x 2 rows of 12544 37.7 /
+  // 36.3, decode of these 38.9 / 30.7 and 33.2 / 30.4; with positional keys 4 x
+  // 16 rows of 4112 (8 batches) 22.8 / 20.5, 8 x 8 rows 24.0 / 20.7.  Below it
+  // (8 batches per wave, 4 bits, 8 x 4 rows of 16K) 30.5 / 30.2 to 32.4.
   const int64_t span_wgs = (rope ? 1 : 2) * kCus;
   const int64_t span_line = span_wgs * kWaves * (rope ? 8 : 12);
   if (wide && n_splits > 1 && batch * n_rows * ((max_seq_len + 15) / 16) >= span_line) {

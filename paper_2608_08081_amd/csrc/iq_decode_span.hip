@@ -199,13 +199,14 @@ __device__ __forceinline__ void span_chunk(SpanState<kBits, kRope>& s, SpanStage
       for (int r = 0; r < 4; ++r) x[r] += xor_lane<8>(x[r]);
       xs = upper ? f32x2_t{x[2], x[3]} : f32x2_t{x[0], x[1]};
     } else {
-      // (s^K (hi + lo) rounded once: the scores' rounding is most of the error)
+      // (s^K (hi + lo) rounded once: the scores' rounding is most of the error;
+      // lo is below 2^10, so that an infinite s^K gives hi's infinity, not NaN)
       const f32x2_t ks = *reinterpret_cast<const f32x2_t*>(&st.ks[16 * i + 4 * grp + rs]);
 #pragma unroll
       for (int j = 0; j < 2; ++j) {
         const float p0 = xor_lane<8>(acc[j]), p2 = xor_lane<8>(acc[2 + j]);
         const float hi = upper ? p2 : acc[j], lo = upper ? acc[2 + j] : p0;
-        xs[j] = __builtin_fmaf(hi, ks[j], lo * ks[j]);
+        xs[j] = __builtin_fmaf(hi, ks[j], lo * fminf(ks[j], 0x1p117f));
       }
     }
     if (!kFull && 16 * i + 16 > nvalid) {
@@ -767,8 +768,10 @@ __global__ __launch_bounds__(merge_threads<kHpw>) void merge_span_kernel(
   const int tid = threadIdx.x;
   const int vshift = group > kHeads ? 1 : 0;
   const int n_rows = n_kv_heads << vshift;
-  const int y = static_cast<int>(blockIdx.x) / (kHeads / kHpw);
-  const int h0 = static_cast<int>(blockIdx.x) % (kHeads / kHpw) * kHpw;
+  // workgroups per row: one, or one for each of its heads
+  const int per = kHpw == 1 ? (group < kHeads ? group : kHeads) : 1;
+  const int y = static_cast<int>(blockIdx.x) / per;
+  const int h0 = static_cast<int>(blockIdx.x) - y * per;
   const int b = blockIdx.y;
   const int g = y >> vshift, vg = y & vshift;
   const int nh = group - kHeads * vg < kHeads ? group - kHeads * vg : kHeads;
@@ -956,11 +959,15 @@ hipError_t launch_decode_span(const SpanPlan& plan, int64_t n_splits, const floa
 #undef IQ_LAUNCH_SPAN
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  // on average at most 16 spans per row: one pass of the 8-head workgroups
-  const bool few = plan.by_rows || plan.workers <= 15 * batch * n_rows;
+  // Workgroups of a whole row for rows of on average at most 16 spans (one pass)
+  // and more than 2 query heads; for 1 or 2 the other heads' share of their
+  // loads is wasted (positional keys, 16 rows of one head, batch of 4, 12 us
+  // short calls: 0.3 us).
+  const bool few = (plan.by_rows || plan.workers <= 15 * batch * n_rows) && group > 2;
   const int runs = plan.by_rows ? 0 : plan.workers;
-  const dim3 mgrid(static_cast<unsigned>(few ? n_rows : n_rows * kHeads),
-                   static_cast<unsigned>(batch));
+  const dim3 mgrid(
+      static_cast<unsigned>(few ? n_rows : n_rows * (group < kHeads ? group : kHeads)),
+      static_cast<unsigned>(batch));
 #define IQ_LAUNCH_SPAN_MERGE(APP_, HPW_)                                                        \
   hipLaunchKernelGGL((merge_span_kernel<APP_, HPW_>), mgrid, dim3(merge_threads<HPW_>), 0,       \
                      stream, partials, quats, out, static_cast<int>(n_kv_heads),                \
