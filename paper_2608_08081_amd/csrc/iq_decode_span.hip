@@ -204,9 +204,15 @@ __device__ __forceinline__ void span_chunk(SpanState<kBits, kRope>& s, SpanStage
       const f32x2_t ks = *reinterpret_cast<const f32x2_t*>(&st.ks[16 * i + 4 * grp + rs]);
 #pragma unroll
       for (int j = 0; j < 2; ++j) {
-        const float p0 = xor_lane<8>(acc[j]), p2 = xor_lane<8>(acc[2 + j]);
-        const float hi = upper ? p2 : acc[j], lo = upper ? acc[2 + j] : p0;
-        xs[j] = __builtin_fmaf(hi, ks[j], lo * fminf(ks[j], 0x1p117f));
+        // (a rotation by 8 in each row of 16 lanes, into its upper or lower half
+        // only; plain floats first, see row_pair)
+        const float f0 = acc[j], f2 = acc[2 + j];
+        const int a0 = __builtin_bit_cast(int, f0), a2 = __builtin_bit_cast(int, f2);
+        const float hi = __builtin_bit_cast(
+            float, __builtin_amdgcn_update_dpp(a0, a2, 0x128, 0xF, 0xC, false));
+        const float lo = __builtin_bit_cast(
+            float, __builtin_amdgcn_update_dpp(a2, a0, 0x128, 0xF, 0x3, false));
+        xs[j] = __builtin_fmaf(hi, ks[j], lo * __builtin_amdgcn_fmed3f(ks[j], 0.f, 0x1p117f));
       }
     }
     if (!kFull && 16 * i + 16 > nvalid) {
