@@ -114,7 +114,7 @@ __device__ __forceinline__ void cross_butterfly8(float (&x)[kDim / 2], int i0, f
 // condition masks, whose readers wait on gfx950 (168 s_nop per half vector
 // were left after scheduling).  The kernel is bound by vector instructions, of
 // which a half vector now has 1321 instead of 1475 (and 89 registers instead
-// of 127): 4 x 8 x 32768 keys and values in fp16 181 -> 168 us, 3.8 TB/s.
+// of 127): 4 x 8 x 32768 keys and values in fp16 178 -> 167 us, 3.9 TB/s.
 // Word w takes one more bit, the sign of `bits`.
 __device__ __forceinline__ uint32_t push_sign(uint32_t w, uint32_t bits) {
   return __builtin_amdgcn_alignbit(w, bits, 31);

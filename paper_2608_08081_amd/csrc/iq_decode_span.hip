@@ -30,8 +30,8 @@
 // which is also what the kernel reaches with its arithmetic taken out (fixed
 // splits: 73.5 us); the arithmetic alone, on cached records, takes 0.85 of
 // the whole, split evenly over the table lookups (LDS), the vector and the
-// matrix units.  Batch-64 step (2048..32768 positions, 2 rows): 84.5 -> 68.4
-// us, on another card 87.7 -> 73.3.
+// matrix units.  Batch-64 step (2048..32768 positions, 2 rows): 81.7 -> 68.0
+// us.
 #include <hip/hip_runtime.h>
 #include <math.h>
 
