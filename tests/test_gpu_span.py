@@ -421,3 +421,52 @@ def test_outlier_among_the_value_scales(ratio):
     err = np.abs(got - ref).max(-1)
     print(f"[outlier {ratio:g}] {err.max():.3e} bound {bound.min():.3e} out {np.abs(ref).max():.3e}")
     assert np.all(err <= bound)
+
+
+@pytest.mark.parametrize("page", [0, 16])
+def test_captured_step_follows_the_lengths(page):
+    """One captured step replayed on short lines (fixed splits) and long ones (equal runs) in turn,
+    with the program's own work between: every replay as the eager call on the same cache."""
+    hkv, group, cap = 2, 8, 2112
+    batch = -(-49152 // (hkv * (cap // 16)))
+    g = torch.Generator(device=DEV).manual_seed(19)
+    shape = (batch * cap // page, hkv, page) if page else (batch, hkv, cap)
+    cache = {}
+    for side in ("k", "v"):
+        cache[f"{side}_codes"] = torch.randint(0, 256, (*shape, 48), generator=g, device=DEV,
+                                               dtype=torch.uint8)
+        cache[f"{side}_norms"] = 14.0 * torch.exp(0.35 * torch.randn(shape, generator=g, device=DEV))
+    tab = torch.randperm(batch * cap // (page or cap), generator=g, device=DEV).int().view(batch, -1)
+    q = torch.randn((batch, hkv * group, 128), generator=g, device=DEV)
+    k, v = (torch.randn((batch, hkv, 128), generator=g, device=DEV) for _ in range(2))
+    quats = api.iq_make_rotation(20, hkv).to(DEV)
+    lens = torch.zeros(batch, dtype=torch.int32, device=DEV)
+    ws = api.alloc_workspace(batch, hkv * group, hkv, cap, DEV)
+    out, ws2 = torch.empty_like(q), torch.empty_like(ws)
+
+    def step(lens, out, ws):
+        if page:
+            api.iq_decode_step_paged(q, k, v, cache, tab, lens, quats, out=out, workspace=ws)
+        else:
+            api.iq_decode_step(q, k, v, *cache.values(), lens, quats, out=out, workspace=ws)
+
+    sizes = [torch.randint(lo, hi, (batch,), generator=g, device=DEV).int()
+             for lo, hi in ((0, 300), (1700, cap - 1), (500, 900), (1500, cap - 1), (0, 40))]
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        step(lens, out, ws)
+    torch.cuda.current_stream().wait_stream(side)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        step(lens, out, ws)
+    for n in sizes:
+        want, eager = torch.empty_like(q), n.clone()
+        lens.copy_(n)
+        out.zero_()
+        graph.replay()
+        step(eager, want, ws2)   # (appends the same token at the same place again)
+        torch.cuda.synchronize()
+        assert torch.equal(out, want) and torch.isfinite(out).all() and out.abs().max() > 0
+        assert torch.equal(lens, n + 1) and torch.equal(lens, eager)
